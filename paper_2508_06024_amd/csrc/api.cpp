@@ -666,28 +666,33 @@ ec2moe_status ec2moe_lowrank_decode(const ec2moe_codec_desc* desc, const float* 
 
 namespace {
 
+// Scratch of one side of the fit (U: n = h, r = r_h; V: n = w, r = r_w)
+struct FitSideWs {
+    size_t gram, y, q1, q, g64, g64part, f;
+};
 struct FitWs {
-    size_t gpart, gram, xt, q, y, q1, qt, g64, g64part, rinv_t, total;
+    size_t gpart, xt, total;
+    FitSideWs side[2];
 };
 
 FitWs fit_ws(const ec2moe_codec_desc* d) {
     const size_t eb = elem_bytes(static_cast<DType>(d->dtype));
-    const size_t n = static_cast<size_t>(std::max(d->h, d->w));
-    const size_t r = static_cast<size_t>(std::max(d->r_h, d->r_w));
     const size_t cells = static_cast<size_t>(std::max(1, d->n_slices)) * d->h * d->w;
     FitWs w{};
     size_t o = 0;
     w.gpart = o; o += up(gemm_split_scratch_bytes());
-    w.gram = o; o += up(n * n * 4);
     w.xt = o; o += up(cells * eb);
-    w.q = o; o += up(n * r * 4);
-    w.y = o; o += up(n * r * 4);
-    w.q1 = o; o += up(n * r * 4);
-    w.qt = o; o += up(n * r * 4);
-    w.g64 = o; o += up(r * r * 8);
-    const int chunks = std::max(gram64_chunks(d->h, static_cast<int>(d->r_h)), gram64_chunks(d->w, static_cast<int>(d->r_w)));
-    w.g64part = o; o += up(static_cast<size_t>(chunks) * r * r * 8);
-    w.rinv_t = o; o += up(r * r * 4);
+    for (int q = 0; q < 2; ++q) {
+        const size_t n = static_cast<size_t>(q == 0 ? d->h : d->w), r = static_cast<size_t>(q == 0 ? d->r_h : d->r_w);
+        FitSideWs& b = w.side[q];
+        b.gram = o; o += up(n * n * 4);
+        b.y = o; o += up(n * r * 4);
+        b.q1 = o; o += up(n * r * 4);
+        b.q = o; o += up(n * r * 4);
+        b.g64 = o; o += up(r * r * 8);
+        b.g64part = o; o += up(static_cast<size_t>(gram64_chunks(static_cast<int>(n), static_cast<int>(r))) * r * r * 8);
+        b.f = o; o += up(chol_factor_bytes(static_cast<int>(r)));
+    }
     w.total = o;
     return w;
 }
@@ -701,39 +706,36 @@ hipError_t dense_gemm(DType dt, OutType ot, const void* tok, const void* wt, int
     return launch_gemm(dt, Epilogue::Store, ot, g, s);
 }
 
-// Q = orth(Y) for Y [n][r] float32 (CholeskyQR2, the first pass into q1); q receives the result.
-hipError_t orthonormalise(float* y, int n, int r, float* q1, float* q, const FitWs& w, void* ws, int32_t* status,
-                          bool& reset, hipStream_t s) {
-    double* g64 = at<double>(ws, w.g64);
-    float* rinv_t = at<float>(ws, w.rinv_t);
-    float* part = at<float>(ws, w.gpart);
-    const float* src = y;
-    for (int pass = 0; pass < 2; ++pass) {
-        float* dst = pass == 0 ? q1 : q;
-        hipError_t e = launch_gram64(src, n, r, at<double>(ws, w.g64part), g64, s);
-        if (e == hipSuccess) e = launch_chol_inv(g64, r, rinv_t, status, reset, s);
-        reset = false;
-        if (e == hipSuccess) e = dense_gemm(DType::F32, OutType::Same, src, rinv_t, n, r, r, dst, "fit_qr", part, s);
+// One side of the subspace iteration
+struct FitSide {
+    int n, r;
+    const float* src;  // the block to orthonormalise, [n][r]
+    float *gram, *y, *q1, *q;
+    double *g64, *g64part;
+    void* f;      // Cholesky factor
+    float* last;  // receives the last iterate [n][r]
+};
+
+// Q = orth(src) of both sides: one Cholesky QR pass into q as [r][n] (the GEMM's weight rows of the
+// next power step), or for the last iterate two passes (CholeskyQR2) into last as [n][r].
+hipError_t orthonormalise(const FitSide (&f)[2], bool last, int32_t* zero_status, int32_t* status, hipStream_t s) {
+    for (int pass = 0; pass < (last ? 2 : 1); ++pass) {
+        GramSide gs[2];
+        CholArgs ca{};
+        SolveArgs sa{};
+        ca.status = status;
+        for (int q = 0; q < 2; ++q) {
+            const float* in = pass == 0 ? f[q].src : f[q].q1;
+            gs[q] = GramSide{in, f[q].n, f[q].r, f[q].g64part, f[q].g64};
+            ca.s[q] = CholSide{f[q].g64, f[q].f, f[q].r};
+            sa.s[q] = SolveSide{in, f[q].f, !last ? f[q].q : (pass == 0 ? f[q].q1 : f[q].last), f[q].n, f[q].r, !last};
+        }
+        hipError_t e = launch_gram64(gs, pass == 0 ? zero_status : nullptr, s);
+        if (e == hipSuccess) e = launch_chol(ca, s);
+        if (e == hipSuccess) e = launch_solve(sa, s);
         if (e != hipSuccess) return e;
-        src = dst;
     }
     return hipSuccess;
-}
-
-// Subspace iteration of one side: gram [n][n] float32, omega [n][r]; the result in q.
-hipError_t fit_side(const float* gram, const float* omega, int n, int r, int iters, const FitWs& w, void* ws,
-                    int32_t* status, bool& reset, hipStream_t s) {
-    float* q = at<float>(ws, w.q);
-    float* y = at<float>(ws, w.y);
-    float* q1 = at<float>(ws, w.q1);
-    float* qt = at<float>(ws, w.qt);
-    hipError_t e = orthonormalise(const_cast<float*>(omega), n, r, q1, q, w, ws, status, reset, s);
-    for (int it = 0; it < iters && e == hipSuccess; ++it) {
-        e = launch_transpose(DType::F32, q, n, r, qt, s);  // Q^T [r][n]: the GEMM's weight rows
-        if (e == hipSuccess) e = dense_gemm(DType::F32, OutType::Same, gram, qt, n, n, r, y, "fit_power", at<float>(ws, w.gpart), s);
-        if (e == hipSuccess) e = orthonormalise(y, n, r, q1, q, w, ws, status, reset, s);
-    }
-    return e;
 }
 
 }  // namespace
@@ -761,10 +763,20 @@ ec2moe_status ec2moe_lowrank_fit(const ec2moe_codec_desc* desc, const void* x, c
     REQUIRE_ALIGNED(x); REQUIRE_ALIGNED(omega_u); REQUIRE_ALIGNED(omega_v); REQUIRE_ALIGNED(u); REQUIRE_ALIGNED(v);
     const DType dt = static_cast<DType>(desc->dtype);
     const int c = desc->n_slices, h = desc->h, wd = desc->w;
-    float* gram = at<float>(ws, w.gram);
     void* xt = at<void>(ws, w.xt);
     float* part = at<float>(ws, w.gpart);
-    bool reset = true;
+    void* const outs[2] = {u, v};
+    FitSide f[2];
+    for (int q = 0; q < 2; ++q) {
+        const FitSideWs& b = w.side[q];
+        f[q].n = q == 0 ? h : wd;
+        f[q].r = q == 0 ? desc->r_h : desc->r_w;
+        f[q].src = q == 0 ? omega_u : omega_v;
+        f[q].gram = at<float>(ws, b.gram); f[q].y = at<float>(ws, b.y); f[q].q1 = at<float>(ws, b.q1);
+        f[q].q = at<float>(ws, b.q); f[q].f = at<void>(ws, b.f);
+        f[q].g64 = at<double>(ws, b.g64); f[q].g64part = at<double>(ws, b.g64part);
+        f[q].last = dt == DType::BF16 ? f[q].q : static_cast<float*>(outs[q]);
+    }
     // A = sum_s X_s X_s^T [h][h]: the mode-1 unfolding times itself (K = c*w)
     const void* xu = x;
     hipError_t e = hipSuccess;
@@ -772,22 +784,20 @@ ec2moe_status ec2moe_lowrank_fit(const ec2moe_codec_desc* desc, const void* x, c
         e = launch_unfold(dt, x, c, h, wd, xt, stream);
         xu = xt;
     }
-    if (e == hipSuccess) e = dense_gemm(dt, OutType::F32, xu, xu, h, c * wd, h, gram, "fit_gram_a", part, stream);
-    if (e == hipSuccess) e = fit_side(gram, omega_u, h, desc->r_h, iters, w, ws, status, reset, stream);
-    if (e == hipSuccess) {
-        const int64_t nu = static_cast<int64_t>(h) * desc->r_h;
-        e = dt == DType::BF16 ? launch_f32_to_bf16(at<float>(ws, w.q), nu, u, stream)
-                              : hipMemcpyAsync(u, at<float>(ws, w.q), nu * 4, hipMemcpyDeviceToDevice, stream);
-    }
+    if (e == hipSuccess) e = dense_gemm(dt, OutType::F32, xu, xu, h, c * wd, h, f[0].gram, "fit_gram_a", part, stream);
     // B = sum_s X_s^T X_s [w][w]: X^T [w][c*h] times itself (K = c*h)
     if (e == hipSuccess) e = launch_transpose(dt, x, c * h, wd, xt, stream);
-    if (e == hipSuccess) e = dense_gemm(dt, OutType::F32, xt, xt, wd, c * h, wd, gram, "fit_gram_b", part, stream);
-    if (e == hipSuccess) e = fit_side(gram, omega_v, wd, desc->r_w, iters, w, ws, status, reset, stream);
-    if (e == hipSuccess) {
-        const int64_t nv = static_cast<int64_t>(wd) * desc->r_w;
-        e = dt == DType::BF16 ? launch_f32_to_bf16(at<float>(ws, w.q), nv, v, stream)
-                              : hipMemcpyAsync(v, at<float>(ws, w.q), nv * 4, hipMemcpyDeviceToDevice, stream);
+    if (e == hipSuccess) e = dense_gemm(dt, OutType::F32, xt, xt, wd, c * h, wd, f[1].gram, "fit_gram_b", part, stream);
+    // both sides in lockstep: orthonormalise the start blocks, then iters steps Q = orth(gram Q)
+    for (int it = 0; it <= iters && e == hipSuccess; ++it) {
+        for (int q = 0; q < 2 && it > 0 && e == hipSuccess; ++q) {
+            e = dense_gemm(DType::F32, OutType::Same, f[q].gram, f[q].q, f[q].n, f[q].n, f[q].r, f[q].y, "fit_power", part, stream);
+            f[q].src = f[q].y;
+        }
+        if (e == hipSuccess) e = orthonormalise(f, it == iters, it == 0 ? status : nullptr, status, stream);
     }
+    for (int q = 0; q < 2 && dt == DType::BF16 && e == hipSuccess; ++q)
+        e = launch_f32_to_bf16(f[q].q, static_cast<int64_t>(f[q].n) * f[q].r, outs[q], stream);
     return hip_status(e, "lowrank_fit launch");
 }
 

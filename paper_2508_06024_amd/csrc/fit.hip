@@ -1,11 +1,18 @@
 // Data-free fitting of the codec projections (Encoder-Decoder based on Low-Rank
 // Compression, Eq. 8 with lambda = 0) for gfx950: the kernels that the matrix-core GEMM
 // does not cover. The fit is subspace iteration on the Gram matrices of the calibration
-// slices (the products run on the GEMM); every iterate is orthonormalised by CholeskyQR2
-// (Yamamoto et al., 2015): G = Y^T Y, G = R^T R, Q = Y R^-1, twice. The Gram matrix and
-// its Cholesky factor are float64, so the factorisation holds for condition numbers of Y
-// up to about 1e7 (float32 would fail near 4e3); the second pass restores the
-// orthogonality the float32 product Y R^-1 loses.
+// slices (the products run on the GEMM); every iterate is orthonormalised by a Cholesky QR
+// (Yamamoto et al., 2015): G = Y^T Y, G = R^T R, Q = Y R^-1. The Gram matrix, its factor and the
+// triangular solve are float64, so the factorisation holds for condition numbers of Y up to
+// about 1e7 (float32 would fail near 4e3) and Q is rounded to float32 once; the last iterate
+// takes a second pass (CholeskyQR2), which leaves it orthonormal to float32 at any of those
+// condition numbers. The iterates before it need only span their subspace, and R from one pass
+// does that as well as from two.
+//
+// The three kernels work on 16 x 16 blocks on the float64 matrix cores. A block in their result
+// layout (lane l: rows 4 v + l / 16 of column l % 16 in register v) is at once the B operand of a
+// product over its rows and, read as the A operand, its own transpose, so no block is ever
+// transposed in memory.
 #include "device_common.h"
 #include "internal.h"
 
@@ -14,286 +21,334 @@
 namespace ec2moe {
 namespace {
 
-constexpr int kGramB = 64;  // output block of the Gram kernel
-constexpr int kGramT = 32;  // rows of Y staged per step
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
-// part[z][i][j] = sum over the rows t of chunk z of y[t][i] * y[t][j] (i, j < r) in float64,
-// rows in order (both triangles add the same products in the same order, so the sum is
-// exactly symmetric). One workgroup per (64x64 block, chunk of tc rows); thread (a, b) owns
-// the 4x4 entries 4a.., 4b...
-__global__ __launch_bounds__(256) void gram64_kernel(const float* __restrict__ y, int n, int r, int tc,
-                                                     double* __restrict__ part) {
-    __shared__ double ys_i[kGramT][kGramB];
-    __shared__ double ys_j[kGramT][kGramB];
-    const int i0 = blockIdx.x * kGramB, j0 = blockIdx.y * kGramB;
-    const int a = threadIdx.x / 16, b = threadIdx.x % 16;
-    const int tb = blockIdx.z * tc, te = min(n, tb + tc);
-    double* g = part + static_cast<int64_t>(blockIdx.z) * r * r;
-    double acc[4][4] = {};
-    for (int t0 = tb; t0 < te; t0 += kGramT) {
-        for (int e = threadIdx.x; e < kGramT * kGramB; e += 256) {
-            const int t = e / kGramB, c = e % kGramB;
-            const bool rowok = t0 + t < te;
-            ys_i[t][c] = rowok && i0 + c < r ? static_cast<double>(y[static_cast<int64_t>(t0 + t) * r + i0 + c]) : 0.0;
-            ys_j[t][c] = rowok && j0 + c < r ? static_cast<double>(y[static_cast<int64_t>(t0 + t) * r + j0 + c]) : 0.0;
-        }
-        __syncthreads();
-        for (int t = 0; t < kGramT; ++t) {
-            double vi[4], vj[4];
+__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// A block's registers in memory: two planes of [64 lanes][2 doubles] (16-byte accesses of
+// consecutive lanes are contiguous).
+struct Block64 {
+    f64x2 v[2][64];
+};
+
+__device__ __forceinline__ f64x4 block_get(const Block64& b, int lane) {
+    const f64x2 lo = b.v[0][lane], hi = b.v[1][lane];
+    return f64x4{lo[0], lo[1], hi[0], hi[1]};
+}
+__device__ __forceinline__ void block_put(Block64& b, int lane, f64x4 x) {
+    b.v[0][lane] = f64x2{x[0], x[1]};
+    b.v[1][lane] = f64x2{x[2], x[3]};
+}
+
+// c + A^T B over 16 rows, both blocks in the result layout
+__device__ __forceinline__ f64x4 block_update(f64x4 c, f64x4 at, f64x4 b) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                vi[q] = ys_i[t][4 * a + q];
-                vj[q] = ys_j[t][4 * b + q];
+    for (int v = 0; v < 4; ++v) c = mfma64(at[v], b[v], c);
+    return c;
+}
+
+// ------------------------------------------------------------------ Gram matrix
+//
+// part[z][i][j] = sum over the rows t of chunk z of y[t][i] * y[t][j] in float64, for the 64 x 64
+// tiles on and above the diagonal (the factorisation reads no others). One workgroup per (tile,
+// chunk of tc rows, side); wave w owns rows 16 w .. of the tile, four blocks. The operands of a
+// step of four rows are one float32 per lane straight from global memory (a row's 16 columns are
+// one 64-byte piece; the waves of a tile share them through the caches), with kGramU steps of
+// loads in flight: the products, 64 cycles each, leave the loads ample time. 4096 x 256: 55 us
+// with float64 FMAs on staged rows.
+constexpr int kGramB = 64;  // tile
+constexpr int kGramU = 8;   // row steps (of 4) whose loads are in flight together
+
+struct GramArgs {
+    GramSide s[2];
+    int tc[2], chunks[2], tiles[2];  // rows per chunk, chunks, 64-column tiles
+    int32_t* zero_status;
+};
+
+__global__ __launch_bounds__(256) void gram64_kernel(GramArgs a) {
+    if (a.zero_status && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) *a.zero_status = 0;
+    const int q = blockIdx.z, tiles = a.tiles[q], r = a.s[q].r;
+    if (static_cast<int>(blockIdx.x) >= tiles * (tiles + 1) / 2 || static_cast<int>(blockIdx.y) >= a.chunks[q]) return;
+    int tj = 0;
+    while ((tj + 1) * (tj + 2) / 2 <= static_cast<int>(blockIdx.x)) ++tj;
+    const int ti = blockIdx.x - tj * (tj + 1) / 2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l16 = lane & 15, g = lane >> 4;
+    const int i0 = ti * kGramB + 16 * wave, j0 = tj * kGramB;
+    if (i0 >= r) return;  // r is a multiple of 16
+    const int tb = blockIdx.y * a.tc[q], te = min(a.s[q].n, tb + a.tc[q]);
+    const float* __restrict__ y = a.s[q].y;
+    int cj[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cj[c] = min(j0 + 16 * c, r - 16) + l16;  // blocks past r repeat the last (not stored)
+    f64x4 acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int t0 = tb; t0 < te; t0 += 4 * kGramU) {
+        float fi[kGramU], fj[kGramU][4];
+#pragma unroll
+        for (int u = 0; u < kGramU; ++u) {
+            const int t = t0 + 4 * u + g;
+            const float* row = y + static_cast<int64_t>(min(t, te - 1)) * r;
+            const float x = row[i0 + l16];
+            fi[u] = t < te ? x : 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float z = row[cj[c]];
+                fj[u][c] = t < te ? z : 0.f;
             }
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[p][q] = fma(vi[p], vj[q], acc[p][q]);
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kGramU; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] = mfma64(static_cast<double>(fi[u]), static_cast<double>(fj[u][c]), acc[c]);
     }
+    double* out = a.s[q].part + static_cast<int64_t>(blockIdx.y) * r * r;
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
+    for (int c = 0; c < 4; ++c)
+        if (j0 + 16 * c < r) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int i = i0 + 4 * a + p, j = j0 + 4 * b + q;
-            if (i < r && j < r) g[static_cast<int64_t>(i) * r + j] = acc[p][q];
+            for (int v = 0; v < 4; ++v) out[static_cast<int64_t>(i0 + 4 * v + g) * r + j0 + 16 * c + l16] = acc[c][v];
         }
 }
 
-// g[e] = sum over chunks z in order of part[z][e] (e < r*r)
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part, int chunks, int64_t rr,
-                                                          double* __restrict__ g) {
-    for (int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; e < rr;
-         e += static_cast<int64_t>(gridDim.x) * 256) {
-        double v = part[e];
-        for (int z = 1; z < chunks; ++z) v += part[z * rr + e];
-        g[e] = v;
+// g[i][j] = sum over chunks z in order of part[z][i][j], for the tiles the products fill
+__global__ __launch_bounds__(256) void gram_reduce_kernel(GramArgs a) {
+    const int q = blockIdx.y, r = a.s[q].r;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= r * r || (e / r) / kGramB > (e % r) / kGramB) return;
+    const double* src = a.s[q].part + e;
+    const int64_t rr = static_cast<int64_t>(r) * r;
+    const int chunks = a.chunks[q];
+    double sum = 0.0;
+    for (int z = 0; z < chunks; z += 16) {
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = z + u < chunks ? src[(z + u) * rr] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sum += v[u];
     }
+    a.s[q].g[e] = sum;
 }
 
-// Cholesky factor and triangular inverse of one r x r float64 Gram matrix (r <= 256, a
-// multiple of 16) in one workgroup of 512 threads, with the matrix held in registers:
-// thread (ti, tj) = (tid / 32, tid % 32) owns the entries (16 a + ti, 32 b + tj) of the
-// blocks (a, b) that meet the upper triangle (a <= 2 b + 1: 72 of the 128 blocks, 144
-// registers). Each of the 2 r steps publishes one row (and column) through LDS, double
-// buffered by the parity of the step, so one barrier per step suffices; every thread then
-// applies the step to its entries with multipliers that are zero where the step changes
-// nothing, so the update is branch-free. The steps run in four phases of 64; a phase
-// leaves out, at compile time, the blocks that none of its steps can change.
-//   factor (right-looking, a rank-1 update per column): with d = A[k][k],
-//     A[i][j] -= A[k][i] A[k][j] / d for i, j > k, and row k becomes R[k][j] = A[k][j] / sqrt(d)
-//     for j >= k (zero left of the diagonal); a pivot that is not positive sets the status
-//     and is replaced by 1;
-//   inverse (Gauss-Jordan elimination on R, in place; the triangle is preserved): with
-//     q = 1 / R[k][k], A[i][j] -= A[i][k] q A[k][j] for i < k < j, column k above the
-//     diagonal becomes -A[i][k] q, and row k becomes q A[k][j] (q on the diagonal).
-// Outputs rinv_t[n][k] = R^-1[k][n] in float32 (the weight layout of the GEMM for Y R^-1).
-constexpr int kCholThreads = 512;
-constexpr int kCholRB = 16;  // row blocks: row 16 a + ti
-constexpr int kCholCB = 8;   // column blocks: column 32 b + tj
+// ------------------------------------------------------------------ Cholesky factor
+//
+// G = R^T R for one r x r float64 Gram matrix (r <= 256, a multiple of 16) per workgroup. The
+// output is what the solve reads: block (k, i) of the upper triangle at f[i (i + 1) / 2 + k],
+// -R_ki in the result layout for k < i, and R_kk^-T as an A operand on the diagonal.
+//
+// What bounds it is the chain of eliminations, so it runs on blocks and the chain has r / 16
+// links instead of r. Per block row k, with Linv = R_kk^-T:
+//   P: row k (in LDS) is multiplied by Linv: R_ki for i > k, which is final and goes out;
+//   U: every block below takes its rank-16 update, G_ji -= R_kj^T R_ki, and the blocks of row
+//      k + 1 go to LDS, while a wave of its own updates the next diagonal block, factors it and
+//      inverts the factor.
+// The blocks of the triangle live in registers, 4 doubles a lane: 11 workers of at most 13,
+// dealt round robin so that those below any k are spread evenly. Everything but R_kk^-T is held
+// negated, so that the updates add. The diagonal wave holds one column of [G_kk | I] per lane
+// and broadcasts the multipliers by lane reads. A pivot that is not positive sets the status and
+// is replaced by 1.
+constexpr int kCholB = 16;
+constexpr int kCholWorkers = 11;
+constexpr int kCholThreads = 64 * (kCholWorkers + 1);
+constexpr int kCholMaxB = 16;  // blocks per side at r = 256
+constexpr int kCholSlots = (kCholMaxB * (kCholMaxB + 1) / 2 + kCholWorkers - 1) / kCholWorkers;
 
-__host__ __device__ constexpr bool chol_kept(int a, int b) { return a <= 2 * b + 1; }
-
-// 1 / sqrt(d) and 1 / p for d, p > 0 (the pivots): the hardware estimates refined by two
-// Newton steps each, to within a few units in the last place of float64
+// 1 / sqrt(d) for d > 0 (the pivots): the hardware estimate y (relative error below 2^-20) with
+// one third-order step, y (1 + e / 2 + 3 e^2 / 8) for e = 1 - d y^2, to within a few units in the
+// last place of float64
 __device__ __forceinline__ double rsqrt64(double d) {
-    double y = __builtin_amdgcn_rsq(d);
-    const double h = 0.5 * d;
-#pragma unroll
-    for (int n = 0; n < 2; ++n) y = y * fma(-h * y, y, 1.5);
-    return y;
-}
-__device__ __forceinline__ double rcp64(double p) {
-    double q = __builtin_amdgcn_rcp(p);
-#pragma unroll
-    for (int n = 0; n < 2; ++n) q = fma(q, fma(-p, q, 1.0), q);
-    return q;
+    const double y = __builtin_amdgcn_rsq(d);
+    const double e = fma(-d * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-// Reads the published values of a step: cols[b] = crow[32 b + tj] and rows[a] = rrow[16 a + ti],
-// every read issued before any is used.
-__device__ __forceinline__ void lds_step(const double* crow, const double* rrow, int tj, int ti,
-                                         double (&cols)[kCholCB], double (&rows)[kCholRB]) {
-#pragma unroll
-    for (int b = 0; b < kCholCB; ++b) cols[b] = crow[32 * b + tj];
-#pragma unroll
-    for (int a = 0; a < kCholRB; ++a) rows[a] = rrow[16 * a + ti];
-#pragma unroll
-    for (int b = 0; b < kCholCB; ++b) asm volatile("" : "+v"(cols[b]));
-#pragma unroll
-    for (int a = 0; a < kCholRB; ++a) asm volatile("" : "+v"(rows[a]));
+__device__ __forceinline__ double lane_read(double v, int lane) {
+    const int2 b = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(b.x, lane), __builtin_amdgcn_readlane(b.y, lane)));
 }
 
 struct CholLds {
-    double row[2][256];
-    double col[2][256];
+    Block64 row[kCholMaxB];    // row k before step P
+    Block64 panel[kCholMaxB];  // row k after it: R_ki for i > k
+    Block64 linv;              // R_kk^-T as the A operand
+    Block64 diag[2];           // the diagonal blocks k + 1 and k + 2, by parity
+    double tmp[kCholB][kCholB + 2];
     int bad;
 };
 
-// Steps k in [64 P, 64 P + 64) of the factor. Row blocks a < 4 P hold finished rows and
-// column blocks b < 2 P only entries left of every pivot of the phase: neither changes.
-template <int P>
-__device__ __forceinline__ void chol_factor_phase(double (&m)[kCholRB][kCholCB], CholLds& sh, int r, int ti, int tj,
-                                                  int tid) {
-    constexpr int A0 = 4 * P, B0 = 2 * P;
-    const int kend = min(r, 64 * P + 64);
-    for (int k = 64 * P; k < kend; ++k) {
-        const int ak = k >> 4, buf = k & 1;
-        if (ti == (k & 15)) {
+// Factors the block x (result layout, symmetric) and publishes R^-T.
+__device__ __forceinline__ void chol_diag(CholLds& sh, f64x4 x, int lane) {
+    asm volatile("" : "+v"(lane));  // keeps the columns of I and the lane tests from being hoisted out of the step loop
+    const int l16 = lane & 15, g = lane >> 4;
 #pragma unroll
-            for (int a = A0; a < kCholRB; ++a)
-                if (a == ak) {
+    for (int v = 0; v < 4; ++v) sh.tmp[4 * v + g][l16] = x[v];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // lanes 0..15: column l16 of the block (its row, by symmetry); the others: column l16 of I
+    double c[kCholB];
 #pragma unroll
-                    for (int b = B0; b < kCholCB; ++b)
-                        if (chol_kept(a, b)) sh.row[buf][32 * b + tj] = m[a][b];
-                }
-        }
-        __syncthreads();
-        double d = sh.row[buf][k];
-        double v[kCholCB], ur[kCholRB];
-        lds_step(sh.row[buf], sh.row[buf], tj, ti, v, ur);
-        if (!(d > 0.0)) {
-            d = 1.0;
-            if (tid == 0) sh.bad = 1;
-        }
-        const double inv_s = rsqrt64(d), inv_d = inv_s * inv_s, sd = d * inv_s;
-        double vm[kCholCB];
+    for (int i = 0; i < kCholB; ++i) c[i] = lane < 16 ? sh.tmp[l16][i] : (i == l16 ? 1.0 : 0.0);
+    bool bad = false;
 #pragma unroll
-        for (int b = B0; b < kCholCB; ++b) vm[b] = 32 * b + tj > k ? v[b] : 0.0;
+    for (int p = 0; p < kCholB; ++p) {
+        const double d = lane_read(c[p], p);
+        const bool pos = d > 0.0;
+        bad |= !pos;
+        const double s = rsqrt64(d);
+        c[p] *= pos ? s : 1.0;
 #pragma unroll
-        for (int a = A0; a < kCholRB; ++a) {
-            const double u = 16 * a + ti > k ? ur[a] * inv_d : 0.0;
+        for (int i = p + 1; i < kCholB; ++i) c[i] = fma(-lane_read(c[p], i), c[p], c[i]);
+    }
+    // lane 16 + j: column j of R^-T, in the A operand at lane 16 (j % 4) + row, register j / 4
+    if (g == 1) {
 #pragma unroll
-            for (int b = B0; b < kCholCB; ++b)
-                if (chol_kept(a, b)) m[a][b] = fma(-u, vm[b], m[a][b]);
-        }
-        if (ti == (k & 15)) {
-#pragma unroll
-            for (int a = A0; a < kCholRB; ++a)
-                if (a == ak) {
-#pragma unroll
-                    for (int b = 0; b < kCholCB; ++b)
-                        if (chol_kept(a, b)) {
-                            const int j = 32 * b + tj;
-                            m[a][b] = j == k ? sd : (j > k ? v[b] * inv_s : 0.0);
-                        }
-                }
-        }
+        for (int i = 0; i < kCholB; ++i) sh.linv.v[l16 >> 3][16 * (l16 & 3) + i][(l16 >> 2) & 1] = c[i];
+        if (bad && l16 == 0) sh.bad = 1;
     }
 }
 
-// Steps k in [64 P, 64 P + 64) of the inverse. Row blocks a > 4 P + 3 lie below every pivot
-// of the phase and column blocks b < 2 P left of it: neither changes.
-template <int P>
-__device__ __forceinline__ void chol_inverse_phase(double (&m)[kCholRB][kCholCB], CholLds& sh, int r, int ti, int tj) {
-    constexpr int A1 = 4 * P + 4, B0 = 2 * P;
-    const int kend = min(r, 64 * P + 64);
-    for (int k = 64 * P; k < kend; ++k) {
-        const int ak = k >> 4, bk = k >> 5, buf = k & 1;
-        if (ti == (k & 15)) {
-#pragma unroll
-            for (int a = 0; a < A1; ++a)
-                if (a == ak) {
-#pragma unroll
-                    for (int b = B0; b < kCholCB; ++b)
-                        if (chol_kept(a, b)) sh.row[buf][32 * b + tj] = m[a][b];
-                }
-        }
-        if (tj == (k & 31)) {
-#pragma unroll
-            for (int b = B0; b < kCholCB; ++b)
-                if (b == bk) {
-#pragma unroll
-                    for (int a = 0; a < A1; ++a)
-                        if (chol_kept(a, b)) sh.col[buf][16 * a + ti] = m[a][b];
-                }
-        }
-        __syncthreads();
-        const double p = sh.row[buf][k];
-        double rq[kCholCB], cr[kCholRB];
-        lds_step(sh.row[buf], sh.col[buf], tj, ti, rq, cr);
-        const double q = rcp64(p);
-        double rqm[kCholCB];
-#pragma unroll
-        for (int b = B0; b < kCholCB; ++b) rqm[b] = 32 * b + tj > k ? rq[b] * q : 0.0;
-#pragma unroll
-        for (int a = 0; a < A1; ++a) {
-            const double c = 16 * a + ti < k ? cr[a] : 0.0;
-#pragma unroll
-            for (int b = B0; b < kCholCB; ++b)
-                if (chol_kept(a, b)) m[a][b] = fma(-c, rqm[b], m[a][b]);
-        }
-        if (tj == (k & 31)) {
-#pragma unroll
-            for (int b = B0; b < kCholCB; ++b)
-                if (b == bk) {
-#pragma unroll
-                    for (int a = 0; a < A1; ++a)
-                        if (chol_kept(a, b)) m[a][b] = 16 * a + ti < k ? -cr[a] * q : m[a][b];
-                }
-        }
-        if (ti == (k & 15)) {
-#pragma unroll
-            for (int a = 0; a < A1; ++a)
-                if (a == ak) {
-#pragma unroll
-                    for (int b = B0; b < kCholCB; ++b)
-                        if (chol_kept(a, b)) {
-                            const int j = 32 * b + tj;
-                            m[a][b] = j == k ? q : (j > k ? rq[b] * q : m[a][b]);
-                        }
-                }
-        }
-    }
-}
-
-__global__ __launch_bounds__(kCholThreads, 1) void chol_inv_kernel(const double* __restrict__ g, int r,
-                                                                   float* __restrict__ rinv_t,
-                                                                   int32_t* __restrict__ status, int reset) {
+__global__ __launch_bounds__(kCholThreads) void chol_kernel(CholArgs args) {
     __shared__ CholLds sh;
-    const int tid = threadIdx.x;
-    const int ti = tid >> 5, tj = tid & 31;
-    double m[kCholRB][kCholCB];
+    const CholSide& side = args.s[blockIdx.x];
+    const int r = side.r, nb = r / kCholB;
+    const double* __restrict__ g64 = side.g;
+    Block64* f = static_cast<Block64*>(side.f);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    const bool worker = wave < kCholWorkers;
+    if (threadIdx.x == 0) sh.bad = 0;
 
-    // the upper triangle of g; zeros below it and outside r (also in the published rows)
+    // slot n of a worker: block (j, i), j <= i, number kCholWorkers n + wave of the column order;
+    // it takes part in the steps k < j (k < j - 1 on the diagonal, whose last update and factor
+    // are the diagonal wave's)
+    int ij[kCholSlots];  // i << 8 | j
+    int lim[kCholSlots];
+    f64x4 m[kCholSlots];
 #pragma unroll
-    for (int a = 0; a < kCholRB; ++a)
+    for (int n = 0; n < kCholSlots; ++n) {
+        const int t = kCholWorkers * n + wave;
+        int i = 0;
+        while ((i + 1) * (i + 2) / 2 <= t) ++i;
+        const int j = t - i * (i + 1) / 2;
+        const bool used = worker && i < nb;
+        ij[n] = __builtin_amdgcn_readfirstlane(used ? i << 8 | j : 0);
+        lim[n] = __builtin_amdgcn_readfirstlane(used ? (i == j ? j - 1 : j) : -1);
+        m[n] = f64x4{0.0, 0.0, 0.0, 0.0};
+        if (used) {
 #pragma unroll
-        for (int b = 0; b < kCholCB; ++b)
-            if (chol_kept(a, b)) {
-                const int i = 16 * a + ti, j = 32 * b + tj;
-                m[a][b] = i <= j && i < r && j < r ? g[static_cast<int64_t>(i) * r + j] : 0.0;
-            }
-    for (int e = tid; e < 2 * 256; e += kCholThreads) {
-        (&sh.row[0][0])[e] = 0.0;
-        (&sh.col[0][0])[e] = 0.0;
-    }
-    if (tid == 0) sh.bad = 0;
-    __syncthreads();
-
-    chol_factor_phase<0>(m, sh, r, ti, tj, tid);
-    chol_factor_phase<1>(m, sh, r, ti, tj, tid);
-    chol_factor_phase<2>(m, sh, r, ti, tj, tid);
-    chol_factor_phase<3>(m, sh, r, ti, tj, tid);
-    chol_inverse_phase<0>(m, sh, r, ti, tj);
-    chol_inverse_phase<1>(m, sh, r, ti, tj);
-    chol_inverse_phase<2>(m, sh, r, ti, tj);
-    chol_inverse_phase<3>(m, sh, r, ti, tj);
-
-    // entries below the diagonal of a kept block hold leftovers of the factor's updates
-#pragma unroll
-    for (int a = 0; a < kCholRB; ++a)
-#pragma unroll
-        for (int b = 0; b < kCholCB; ++b) {
-            const int i = 16 * a + ti, j = 32 * b + tj;
-            if (i < r && j < r)
-                rinv_t[static_cast<int64_t>(j) * r + i] = chol_kept(a, b) && i <= j ? static_cast<float>(m[a][b]) : 0.f;
+            for (int v = 0; v < 4; ++v) m[n][v] = -g64[static_cast<int64_t>(16 * j + 4 * v + g) * r + 16 * i + l16];
+            if (i == j && i < 2) block_put(sh.diag[i], lane, m[n]);
+            else if (j == 0) block_put(sh.row[i], lane, m[n]);
         }
+    }
     __syncthreads();
-    if (tid == 0 && status) {
-        if (reset) *status = sh.bad;
-        else if (sh.bad) *status = 1;
+    if (!worker) chol_diag(sh, -block_get(sh.diag[0], lane), lane);
+    __syncthreads();
+
+    for (int k = 0; k < nb; ++k) {
+        const f64x4 la = block_get(sh.linv, lane);
+        for (int b = k + wave; b < nb; b += kCholWorkers + 1) {
+            f64x4 x = la;
+            if (b > k) {
+                const f64x4 y = block_get(sh.row[b], lane);
+                x = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x = mfma64(la[v], y[v], x);
+                block_put(sh.panel[b], lane, x);
+            }
+            block_put(f[b * (b + 1) / 2 + k], lane, x);
+        }
+        if (k + 1 == nb) break;
+        __syncthreads();
+        if (worker) {
+#pragma unroll
+            for (int n = 0; n < kCholSlots; ++n) {
+                if (k >= lim[n]) continue;
+                const int i = ij[n] >> 8, j = ij[n] & 255;
+                m[n] = block_update(m[n], block_get(sh.panel[j], lane), block_get(sh.panel[i], lane));
+                if (i == j) {
+                    if (j == k + 2) block_put(sh.diag[k & 1], lane, m[n]);
+                } else if (j == k + 1) {
+                    block_put(sh.row[i], lane, m[n]);
+                }
+            }
+        } else {
+            const f64x4 x = block_get(sh.panel[k + 1], lane);
+            chol_diag(sh, -block_update(block_get(sh.diag[(k + 1) & 1], lane), x, x), lane);
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && args.status && sh.bad) atomicOr(args.status, 1);
+}
+
+// ------------------------------------------------------------------ Q = Y R^-1
+//
+// Forward substitution on Q^T = R^-T Y^T without ever forming the inverse: a wave holds 16 rows of
+// Y as the 16 x 16 blocks of Y^T in float64 registers; per block row k, Q^T_k = R_kk^-T Y^T_k and
+// Y^T_j -= R_kj^T Q^T_k for j > k (as many products as a multiplication by the triangular
+// inverse, which would cost the factorisation twice its products). The factor's row k + 1 is
+// loaded while row k is applied from LDS. Out: float32 [n][r], or [r][n] when transposed.
+constexpr int kSolveWaves = 4;
+
+__global__ __launch_bounds__(64 * kSolveWaves, 1) void solve_kernel(SolveArgs args) {
+    __shared__ Block64 fr[2][kCholMaxB];
+    const SolveSide& side = args.s[blockIdx.y];
+    const int n = side.n, r = side.r, nb = r / kCholB;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, g = lane >> 4;
+    if (static_cast<int>(blockIdx.x) * 16 * kSolveWaves >= n) return;
+    const Block64* f = static_cast<const Block64*>(side.f);
+    const int t = (blockIdx.x * kSolveWaves + wave) * 16 + l16;
+    const bool live = t < n;
+    const float* __restrict__ yrow = side.y + static_cast<int64_t>(min(t, n - 1)) * r + g;
+    f64x4 m[kCholMaxB];
+#pragma unroll
+    for (int j = 0; j < kCholMaxB; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) m[j][v] = j < nb ? static_cast<double>(yrow[16 * j + 4 * v]) : 0.0;
+
+    // row k of the factor: blocks (k, j), j >= k; thread t moves 16-byte piece t % 128 of blocks
+    // t / 128 + 2 q past k
+    constexpr int Q = kCholMaxB * 128 / (64 * kSolveWaves);
+    const int piece = tid & 127, b0 = tid >> 7;
+    f64x2 st[Q];
+    auto load = [&](int k) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int j = k + b0 + 2 * q;
+            if (j < nb) st[q] = (&f[j * (j + 1) / 2 + k].v[0][0])[piece];
+        }
+    };
+    load(0);
+#pragma unroll
+    for (int k = 0; k < kCholMaxB; ++k) {
+        if (k < nb) {
+            Block64* cur = fr[k & 1];
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (k + b0 + 2 * q < nb) (&cur[k + b0 + 2 * q].v[0][0])[piece] = st[q];
+            __syncthreads();
+            if (k + 1 < nb) load(k + 1);
+            const f64x4 la = block_get(cur[k], lane);
+            f64x4 x = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x = mfma64(la[v], m[k][v], x);
+#pragma unroll
+            for (int j = k + 1; j < kCholMaxB; ++j)
+                if (j < nb) m[j] = block_update(m[j], block_get(cur[j], lane), x);  // the factor's blocks are -R_kj
+            if (live) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * k + 4 * v + g;
+                    const int64_t at = side.transposed ? static_cast<int64_t>(i) * n + t : static_cast<int64_t>(t) * r + i;
+                    side.out[at] = static_cast<float>(x[v]);
+                }
+            }
+        }
     }
 }
 
@@ -315,32 +370,51 @@ __global__ __launch_bounds__(256) void unfold_kernel(const T* __restrict__ x, in
 }  // namespace
 
 int gram64_chunks(int n, int r) {
-    const int blocks = ((r + kGramB - 1) / kGramB) * ((r + kGramB - 1) / kGramB);
-    const int want = std::max(1, 256 / blocks);  // about one workgroup per CU
-    const int tc = std::max(kGramT, (n + want - 1) / want);
+    const int tiles = (r + kGramB - 1) / kGramB;
+    const int want = std::max(1, 256 / (tiles * (tiles + 1) / 2));  // about one workgroup per CU and side
+    const int tc = std::max(4 * kGramU, (n + want - 1) / want);
     return (n + tc - 1) / tc;
 }
 
-hipError_t launch_gram64(const float* y, int n, int r, double* part, double* g, hipStream_t s) {
-    const int chunks = gram64_chunks(n, r);
-    const int tc = (n + chunks - 1) / chunks;
-    dim3 grid((r + kGramB - 1) / kGramB, (r + kGramB - 1) / kGramB, chunks);
+hipError_t launch_gram64(const GramSide (&sides)[2], int32_t* zero_status, hipStream_t s) {
+    GramArgs a{};
+    a.zero_status = zero_status;
+    int pairs = 0, chunks = 0, rr = 0;
+    for (int q = 0; q < 2; ++q) {
+        a.s[q] = sides[q];
+        a.chunks[q] = gram64_chunks(sides[q].n, sides[q].r);
+        a.tc[q] = (sides[q].n + a.chunks[q] - 1) / a.chunks[q];
+        a.tiles[q] = (sides[q].r + kGramB - 1) / kGramB;
+        pairs = std::max(pairs, a.tiles[q] * (a.tiles[q] + 1) / 2);
+        chunks = std::max(chunks, a.chunks[q]);
+        rr = std::max(rr, sides[q].r * sides[q].r);
+    }
     {
         ProfileScope prof("fit_gram", s);
-        hipLaunchKernelGGL(gram64_kernel, grid, dim3(256), 0, s, y, n, r, tc, part);
+        hipLaunchKernelGGL(gram64_kernel, dim3(pairs, chunks, 2), dim3(256), 0, s, a);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t rr = static_cast<int64_t>(r) * r;
     ProfileScope prof("fit_gram_reduce", s);
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3(static_cast<unsigned>(std::min<int64_t>((rr + 255) / 256, 1024))),
-                       dim3(256), 0, s, part, chunks, rr, g);
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3((rr + 255) / 256, 2), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_chol_inv(const double* g, int r, float* rinv_t, int32_t* status, bool reset, hipStream_t s) {
+size_t chol_factor_bytes(int r) {
+    const size_t nb = static_cast<size_t>(r) / kCholB;
+    return nb * (nb + 1) / 2 * sizeof(Block64);
+}
+
+hipError_t launch_chol(const CholArgs& a, hipStream_t s) {
     ProfileScope prof("fit_chol", s);
-    hipLaunchKernelGGL(chol_inv_kernel, dim3(1), dim3(kCholThreads), 0, s, g, r, rinv_t, status, reset ? 1 : 0);
+    hipLaunchKernelGGL(chol_kernel, dim3(2), dim3(kCholThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_solve(const SolveArgs& a, hipStream_t s) {
+    const int rows = std::max(a.s[0].n, a.s[1].n);
+    ProfileScope prof("fit_qr", s);
+    hipLaunchKernelGGL(solve_kernel, dim3((rows + 16 * kSolveWaves - 1) / (16 * kSolveWaves), 2), dim3(64 * kSolveWaves), 0, s, a);
     return hipGetLastError();
 }
 

@@ -105,14 +105,43 @@ hipError_t launch_encode_fused(const EncArgs& a, float* z, hipStream_t s);
 hipError_t launch_codec_prep(const float* z, int64_t nz, void* zb, int n, int w, int h, int32_t* seg_w,
                              int32_t* rows_w, int32_t* seg_h, int32_t* rows_h, hipStream_t s);
 // ---------------------------------------------------------------- codec fitting
-// g = y^T y in float64 (y [n][r] float32, g [r][r]) through per-chunk partials part
-// ([gram64_chunks(n, r)][r][r] float64) added in chunk order
+// The fit runs its two sides (U and V) in lockstep: each launch below takes both.
+// g = y^T y in float64 (y [n][r] float32, g [r][r], the 64 x 64 tiles on and above the diagonal)
+// through per-chunk partials part ([gram64_chunks(n, r)][r][r] float64) added in chunk order.
+// zero_status (device, or null) is set to 0. r <= 256, a multiple of 16, here and below.
+struct GramSide {
+    const float* y;
+    int n, r;
+    double* part;
+    double* g;
+};
 int gram64_chunks(int n, int r);
-hipError_t launch_gram64(const float* y, int n, int r, double* part, double* g, hipStream_t s);
-// g = R^T R (Cholesky, float64, r <= 256 a multiple of 16; g is read only) and
-// rinv_t[n][k] = (R^-1)[k][n] in float32. *status: 1 if a pivot was not positive (set to 0
-// first when reset).
-hipError_t launch_chol_inv(const double* g, int r, float* rinv_t, int32_t* status, bool reset, hipStream_t s);
+hipError_t launch_gram64(const GramSide (&sides)[2], int32_t* zero_status, hipStream_t s);
+// g = R^T R (Cholesky, float64; g is read only); f (chol_factor_bytes, 16-byte aligned) receives
+// the factor in the form launch_solve reads. status (device, or null): set to 1 if a pivot was not
+// positive, else left alone.
+struct CholSide {
+    const double* g;
+    void* f;
+    int r;
+};
+struct CholArgs {
+    CholSide s[2];
+    int32_t* status;
+};
+size_t chol_factor_bytes(int r);
+hipError_t launch_chol(const CholArgs& a, hipStream_t s);
+// out = y R^-1 (y [n][r] float32, float64 arithmetic, rounded once): [n][r], or [r][n] when transposed
+struct SolveSide {
+    const float* y;
+    const void* f;
+    float* out;
+    int n, r, transposed;
+};
+struct SolveArgs {
+    SolveSide s[2];
+};
+hipError_t launch_solve(const SolveArgs& a, hipStream_t s);
 // xu [h][c*w] = the slices [c][h][w] side by side (w a multiple of 16 bytes)
 hipError_t launch_unfold(DType dt, const void* x, int c, int h, int w, void* xu, hipStream_t s);
 

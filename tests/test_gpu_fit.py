@@ -60,6 +60,41 @@ def test_fit_matches_oracle_iteration(c, h, w, rh, rw, dt, iters, tol):
         say(f"  {name}: projector error {e:.2e}, orthonormality {o:.2e}")
 
 
+@pytest.mark.parametrize("c,h,w,rh,rw,iters", [
+    (1, 72, 128, 16, 32, 1),      # one block; rows that end inside a 16-row block and a 64-row group
+    (8, 17 * 8, 128, 112, 16, 2),  # a Gram tile of 48 columns
+    (1, 264, 1024, 240, 208, 1),  # the last block row but one; several row chunks
+    (2, 32, 256, 32, 256, 0),     # sides of very different sizes; no power step
+])
+def test_fit_block_edges_match_oracle_iteration(c, h, w, rh, rw, iters):
+    """Edges of the blocked orthonormalisation: the basis itself against the oracle's (its columns
+    are fixed by the positive diagonal of R). The slices' spectrum spans a factor 160, its Gram
+    matrix's 2.6e4; float32 products with it leave about 2.6e4 * 6e-8 = 1.5e-3 in the worst column."""
+    xs, x64 = _slices(c, h, w, min(h, w) // 2, W.F32, seed=h + rh)
+    ou, ov = _omega(h, rh, 1), _omega(w, rw, 2)
+    u, v, status = E.lowrank_fit(up(xs, W.F32), up_f32(ou), up_f32(ov), iters)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    ru, rv = O.codec_fit_subspace(x64, ou.astype(np.float64), ov.astype(np.float64), iters)
+    for g, ref, name in ((down(u), ru, "U"), (down(v), rv, "V")):
+        assert np.max(np.abs(g.T @ g - np.eye(g.shape[1]))) <= 1e-6, name
+        assert np.max(np.abs(g - ref)) <= (1e-6 if iters == 0 else 1.5e-3), name
+
+
+def test_fit_ill_conditioned_iterates_stay_orthonormal():
+    """Singular values from 1 to 1e-3: the products with the Gram matrix have condition numbers
+    near 1e6, and one Cholesky QR pass leaves about (1e6)^2 * 2^-53 = 1e-4 of orthogonality; the
+    last iterate's second pass restores it to float32."""
+    n, r = 256, 256
+    p, q = W.haar_orthonormal(3, (1,), n, n), W.haar_orthonormal(3, (2,), n, n)
+    x = ((p * np.logspace(0, -3, n)) @ q.T).astype(np.float32)
+    u, v, status = E.lowrank_fit(up(x, W.F32), up_f32(_omega(n, r, 1)), up_f32(_omega(n, r, 2)), 1)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    for g in (down(u), down(v)):
+        assert np.max(np.abs(g.T @ g - np.eye(r))) <= 1e-6
+
+
 def test_fit_full_size_matches_oracle_iteration():
     """A 4096 x 4096 calibration block at rank 256, one iteration: its Gram products are large
     enough for the 256 x 256 matrix-core tile with float32 output (the only path that uses that

@@ -161,7 +161,8 @@ struct CodecWs {
     // encode: V^T, P = X V (float32), per-chunk partial sums of U^T P
     size_t vt, p, epart, enc_total;
     int tc;      // tokens per chunk of the U^T P contraction
-    bool fused;  // bf16 layers of whole 64-token and 64-column tiles: P and U^T P in one kernel
+    bool fused;  // bf16 layers: P and U^T P in one kernel
+    int ks;      // its shares of the width
     bool small;  // at most 64 tokens per slice: the small-batch encoder and decoder
     // decode: Z rounded to the layer dtype (bf16 only), W = V_hat Z^T per slice, and the segment
     // offsets and row maps of the grouped products over a batch of slices
@@ -177,16 +178,13 @@ int codec_batch(const ec2moe_codec_desc* d) {
     return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({fit, kMaxCodecBatch, std::max(1, d->n_slices)})));
 }
 
-// Token chunk of the U^T P contraction over (slice, chunk, 64-column block) workgroups:
-// bfloat16 layers (three bf16 products per float32 one, about 1/5 of the float32 matrix-core
-// time) aim at 128 workgroups of whole 64-token stages, halving the partial sums; float32
-// layers at one workgroup per CU, in multiples of 4 tokens.
-int utp_chunk(int h, int r_w, int slices, DType dt) {
+// Token chunk of the U^T P contraction of float32 layers over (slice, chunk, 64-column block)
+// workgroups: one workgroup per CU, in multiples of 4 tokens.
+int utp_chunk(int h, int r_w, int slices) {
     const int col_blocks = (r_w + 63) / 64;
-    const bool bf16 = dt == DType::BF16;
-    const int target = std::max(1, (bf16 ? 128 : 256) / (col_blocks * slices));
+    const int target = std::max(1, 256 / (col_blocks * slices));
     const int tc = (std::max(1, h) + target - 1) / target;
-    return bf16 ? (tc + 63) & ~63 : (tc + 3) & ~3;
+    return (tc + 3) & ~3;
 }
 
 CodecWs codec_ws(const ec2moe_codec_desc* d) {
@@ -194,11 +192,12 @@ CodecWs codec_ws(const ec2moe_codec_desc* d) {
     CodecWs w{};
     w.batch = codec_batch(d);
     const size_t nb = static_cast<size_t>(w.batch);
-    w.tc = utp_chunk(d->h, d->r_w, w.batch, static_cast<DType>(d->dtype));
+    w.tc = utp_chunk(d->h, d->r_w, w.batch);
     w.small = codec_small_ok(d->h, d->w, d->r_h, d->r_w);
-    w.fused = !w.small && encode_fused_ok(static_cast<DType>(d->dtype), d->h, d->w, d->r_h, d->r_w);
-    // partial sums of U^T P: per token chunk, or per 64-token tile of the fused encoder
-    const size_t chunks = w.fused ? static_cast<size_t>(d->h) / 64
+    w.fused = !w.small && d->dtype == EC2MOE_BF16;
+    w.ks = w.fused ? encode_splits(d->h, d->w, d->r_w, w.batch) : 1;
+    // partial sums of U^T P: per token chunk, or per 64-token tile and share of the width
+    const size_t chunks = w.fused ? (static_cast<size_t>(d->h) + 63) / 64 * w.ks
                                   : (static_cast<size_t>(std::max(1, d->h)) + w.tc - 1) / w.tc;
     size_t o = 0;
     w.gpart = o; o += up(gemm_split_scratch_bytes());
@@ -549,7 +548,7 @@ ec2moe_status ec2moe_lowrank_encode(const ec2moe_codec_desc* desc, const void* x
         if (w.fused) {
             EncArgs a{};
             a.x = static_cast<const char*>(x) + c0 * slice_bytes; a.v = v; a.u = u; a.part = at<float>(ws, w.epart);
-            a.h = desc->h; a.w = desc->w; a.rh = desc->r_h; a.rw = desc->r_w; a.slices = nc;
+            a.h = desc->h; a.w = desc->w; a.rh = desc->r_h; a.rw = desc->r_w; a.slices = nc; a.ks = w.ks;
             e = launch_encode_fused(a, z + static_cast<size_t>(c0) * desc->r_h * desc->r_w, stream);
             continue;
         }
@@ -566,7 +565,7 @@ ec2moe_status ec2moe_lowrank_encode(const ec2moe_codec_desc* desc, const void* x
         UtpArgs a{};
         a.u = u; a.p = p; a.T = desc->h; a.rh = desc->r_h; a.rw = desc->r_w; a.tc = w.tc; a.slices = nc;
         a.part = at<float>(ws, w.epart); a.z = z + static_cast<size_t>(c0) * desc->r_h * desc->r_w;
-        e = launch_utp(dt, a, stream);
+        e = launch_utp(a, stream);
     }
     return hip_status(e, "lowrank_encode launch");
 }

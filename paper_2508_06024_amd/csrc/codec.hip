@@ -1,8 +1,7 @@
 // Kernels of the low-rank codec (Encoder-Decoder based on Low-Rank Compression) for gfx950:
-// a tiled transpose; the fused encoder of bf16 layers (P = X V and its share of Z = U^T P in
-// one workgroup per 64 x 64 tile of P); the contraction Z = U^T P of the other shapes at
-// float32 accuracy (P = X V in float32; bfloat16 U on the bf16 matrix cores with P split in
-// three bf16 planes, float32 U on the float32 matrix cores); the in-order reduction of the
+// a tiled transpose; the fused encoder of bf16 layers (a share of P = X V and its part of
+// Z = U^T P in one workgroup per 64 x 64 tile of P); the contraction Z = U^T P of float32
+// layers on the float32 matrix cores; the in-order reduction of the
 // partial sums over token tiles or chunks; the small-batch encoder and decoder (at most 64
 // tokens per slice, float32 throughout); the decoder's first product W = V_hat bf16(Z)^T of
 // bf16 layers in one launch; and the float32 -> bfloat16 rounding of Z for the decoder's
@@ -172,170 +171,32 @@ __global__ __launch_bounds__(256) void utp_kernel(UtpArgs g) {
             }
 }
 
-// Z = U^T P with bfloat16 U on the bfloat16 matrix cores at float32 accuracy. Each float32
-// value of P is split exactly into three bfloat16 values, p = hi + mid + lo up to 2^-27 |p|
-// (hi = bf16(p), mid = bf16(p - hi), lo = bf16(p - hi - mid); each difference is exact in
-// float32), and the three products with U, all exact in float32, are accumulated in
-// float32: the same order of accuracy as a float32 contraction, at 3/16 of its matrix-core
-// cost. Tokens are the contraction axis, so a stage of 64 tokens is staged transposed in
-// LDS: U^T as [r][t] rows (an 8x8 register transpose of 16-byte loads) and each plane of P
-// as [c][t] rows, 128 bytes per row with the GEMM's chunk swizzle (chunk i of row R at
-// i ^ ((R >> 1) & 7)). Wave w owns rows 64 w .. 64 w + 63 of this workgroup's 64 columns:
-// 2 x 2 blocks of v_mfma_f32_32x32x16_bf16 (lane l: column l % 32 of a block, rows
-// 8 (q / 4) + 4 (l / 32) + q % 4 in register q). Tokens past the chunk are zero in every
-// operand. Partials per token chunk as in utp_kernel.
-constexpr int kU3T = 64;  // tokens per LDS stage
-constexpr int kU3C = 64;  // columns of P per workgroup
-
-__device__ __forceinline__ uint32_t bf16_pair(uint4 a, uint4 b, int j) {
-    const uint32_t wa = (&a.x)[j >> 1] >> (16 * (j & 1));
-    const uint32_t wb = (&b.x)[j >> 1] >> (16 * (j & 1));
-    return (wa & 0xffffu) | (wb << 16);
-}
-
-__global__ __launch_bounds__(256) void utp3_kernel(UtpArgs g) {
-    __shared__ __attribute__((aligned(1024))) char lds_u[256 * 128];      // U^T [r][64 tokens]
-    __shared__ __attribute__((aligned(1024))) char lds_p[3 * kU3C * 128];  // P^T planes [3][c][64 tokens]
-    const int c0 = blockIdx.x * kU3C;
-    const int tb = blockIdx.y * g.tc;
-    const int te = min(g.T, tb + g.tc);
-    const float* ps = g.p + static_cast<int64_t>(blockIdx.z) * g.T * g.rw;
-    const bf16_t* u = static_cast<const bf16_t*>(g.u);
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, lh = lane >> 5;
-    const int sw = (l32 >> 1) & 7;
-    const int rbase = wave * 64;
-    const bool active = rbase < g.rh;
-    const int rgroups = ((g.rh + 63) & ~63) / 8;  // 8-row groups of U^T staged (zeros past r_h)
-
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-
-    // Per stage each thread holds at most one U item (8 tokens x 8 rows: 8 * rgroups <= 256)
-    // and one P item (8 tokens x 2 columns). The next stage's loads are issued before this
-    // stage's matrix-core work, so they fly while it runs.
-    const bool has_u = tid < 8 * rgroups;
-    const int urg = tid % rgroups, utg = tid / rgroups;
-    const int pcg = tid % 32, ptg = tid / 32;
-    const int pc = c0 + pcg * 2;
-    uint4 rowv[8];
-    float2 pv[8];
-    auto load_stage = [&](int t0) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int t = t0 + utg * 8 + q;
-            rowv[q] = (has_u && t < te && urg * 8 < g.rh) ? ldg16(u + static_cast<int64_t>(t) * g.rh + urg * 8)
-                                                          : make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int t = t0 + ptg * 8 + q;
-            pv[q] = (t < te && pc < g.rw) ? *reinterpret_cast<const float2*>(ps + static_cast<int64_t>(t) * g.rw + pc)
-                                          : make_float2(0.f, 0.f);
-        }
-    };
-    if (tb < te) load_stage(tb);
-    for (int t0 = tb; t0 < te; t0 += kU3T) {
-        // U^T rows r0 .. r0 + 7, 8 tokens of group utg: an 8 x 8 transpose in registers
-        if (has_u) {
-            const int r0 = urg * 8;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int R = r0 + j;
-                const uint4 o = make_uint4(bf16_pair(rowv[0], rowv[1], j), bf16_pair(rowv[2], rowv[3], j),
-                                           bf16_pair(rowv[4], rowv[5], j), bf16_pair(rowv[6], rowv[7], j));
-                *reinterpret_cast<uint4*>(lds_u + R * 128 + ((utg ^ ((R >> 1) & 7)) * 16)) = o;
-            }
-        }
-        // P^T planes: columns pc, pc + 1, each value split into hi, mid, lo
-#pragma unroll
-        for (int cc = 0; cc < 2; ++cc) {
-            uint32_t hw[4], mw[4], lw[4];
-#pragma unroll
-            for (int q = 0; q < 8; q += 2) {
-                uint32_t hb[2], mb[2], lb[2];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const float v = cc ? pv[q + e].y : pv[q + e].x;
-                    const uint16_t h = f32_to_bf16(v);
-                    const float r1 = v - bf16_to_f32(h);
-                    const uint16_t m = f32_to_bf16(r1);
-                    const float r2 = r1 - bf16_to_f32(m);
-                    hb[e] = h;
-                    mb[e] = m;
-                    lb[e] = f32_to_bf16(r2);
-                }
-                hw[q / 2] = hb[0] | (hb[1] << 16);
-                mw[q / 2] = mb[0] | (mb[1] << 16);
-                lw[q / 2] = lb[0] | (lb[1] << 16);
-            }
-            const int R = pcg * 2 + cc;
-            const int off = R * 128 + ((ptg ^ ((R >> 1) & 7)) * 16);
-            *reinterpret_cast<uint4*>(lds_p + 0 * kU3C * 128 + off) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-            *reinterpret_cast<uint4*>(lds_p + 1 * kU3C * 128 + off) = make_uint4(mw[0], mw[1], mw[2], mw[3]);
-            *reinterpret_cast<uint4*>(lds_p + 2 * kU3C * 128 + off) = make_uint4(lw[0], lw[1], lw[2], lw[3]);
-        }
-        __syncthreads();
-        if (t0 + kU3T < te) load_stage(t0 + kU3T);
-        if (active) {
-#pragma unroll
-            for (int s = 0; s < kU3T / 16; ++s) {
-                const int ch = ((2 * s + lh) ^ sw) * 16;
-                uint4 a[2], b[3][2];
-#pragma unroll
-                for (int rb = 0; rb < 2; ++rb) a[rb] = *reinterpret_cast<const uint4*>(lds_u + (rbase + rb * 32 + l32) * 128 + ch);
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb)
-                        b[j][cb] = *reinterpret_cast<const uint4*>(lds_p + (j * kU3C + cb * 32 + l32) * 128 + ch);
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-#pragma unroll
-                    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                        for (int cb = 0; cb < 2; ++cb)
-                            acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                __builtin_bit_cast(bf16x8, a[rb]), __builtin_bit_cast(bf16x8, b[j][cb]), acc[rb][cb], 0, 0,
-                                0);
-            }
-        }
-        __syncthreads();
-    }
-    if (!active) return;
-    float* part = g.part + (static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y) * g.rh * g.rw;
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int r = rbase + rb * 32 + 8 * (q / 4) + 4 * lh + (q % 4);
-                const int c = c0 + cb * 32 + l32;
-                if (r < g.rh && c < g.rw) part[static_cast<int64_t>(r) * g.rw + c] = acc[rb][cb][q];
-            }
-}
-
 // ------------------------------------------------------------------ fused encoder (bf16 layers)
 //
-// One workgroup per (64-token tile, 64-column tile) of P = X V: the tile's products over the
-// whole model width (no split along it), then at once its share of Z = U^T P,
-//   part[s][tt][r][c] = sum over the tile's 64 tokens t of U[t][r] P[t][c],
-// which split_reduce_kernel adds over the token tiles in order. X and V (as stored, [w][r_w])
-// stream through a ring of four LDS stages of 128 model columns (32 KB: 64 token rows of 256
-// bytes, and the 128 rows of V for those model columns, 128 bytes each: the tile's 64 columns)
-// filled by buffer_load ... lds, so three stages are in flight while one is consumed. V's
-// operand fragments need 8 consecutive model columns per lane, which run down the staged
-// rows: the gfx950 transposing LDS read (ds_read_b64_tr_b16) gathers them, 4 rows at a time. Eight waves: wave w computes the 32x32 block (w & 1, (w >> 1) & 1) of the
-// P tile over the even (w < 4) or odd (w >= 4) 16-column steps of each stage; the two halves
-// are added once at the end. The P tile is then split exactly into three bf16 planes
-// (hi + mid + lo) and, with U^T, staged in LDS for the bf16 matrix cores, as in utp3_kernel.
+// One workgroup per (64-token tile, 64-column tile, share of the width) of P = X V: the tile's
+// products over its share, then at once that share's part of Z = U^T P,
+//   part[s][tt][kq][r][c] = sum over the tile's tokens t of U[t][r] P_kq[t][c],
+// which split_reduce_kernel adds over token tiles and shares in order (Z is linear in P, so the
+// shares of P need not be added first). X and V (as stored, [w][r_w]) stream through a ring of
+// four LDS stages of 128 model columns (32 KB: 64 token rows of 256 bytes, and the 128 rows of V
+// for those model columns, 128 bytes each: the tile's 64 columns) filled by buffer_load ... lds,
+// so three stages are in flight while one is consumed. V's operand fragments need 8 consecutive
+// model columns per lane, which run down the staged rows: the gfx950 transposing LDS read
+// (ds_read_b64_tr_b16) gathers them, 4 rows at a time. Eight waves, one k-step of every stage
+// each; their sums meet in LDS. The P tile is then split exactly into three bf16 planes, p = hi +
+// mid + lo up to 2^-27 |p| (hi = bf16(p), mid = bf16(p - hi), lo = bf16(p - hi - mid); each
+// difference is exact in float32), whose products with U are exact in float32: the accuracy of a
+// float32 contraction at 3/16 of its matrix-core cost. U^T [r][t] (an 8x8 register transpose of
+// 16-byte loads) and the planes [c][t] are staged as 128-byte rows, chunk i of row R at
+// i ^ ((R >> 1) & 7).
+//
+// What bounds it: with a tile per CU (4096 x 4096, ranks 256: 256 tiles) the 268 MB that the CUs
+// pull from L2, 23 us of the 26.5 us call; halving the LDS reads of the main loop (a wave used to
+// take one 32 x 32 block of every other k-step) left it at 26.5 us. With few tiles it is the
+// serial walk over the width, hence the shares. Ragged tiles (rows and columns past the end repeat
+// the last one and are dropped) took a transpose, a split-K GEMM, its reduction, U^T P and another
+// reduction before: 1000 x 2048 ranks 128, 26.1 -> 13.4 us; 100 x 4096 ranks 64 x 256, 26.4 -> 11.6;
+// 2047 x 4096 ranks 256, 32.6 -> 23.0.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -346,6 +207,12 @@ __device__ void raw_buffer_load_lds(i32x4 rsrc, lds_void* lds, int size, int vof
                                     int aux) __asm("llvm.amdgcn.raw.buffer.load.lds");
 
 namespace {
+
+__device__ __forceinline__ uint32_t bf16_pair(uint4 a, uint4 b, int j) {
+    const uint32_t wa = (&a.x)[j >> 1] >> (16 * (j & 1));
+    const uint32_t wb = (&b.x)[j >> 1] >> (16 * (j & 1));
+    return (wa & 0xffffu) | (wb << 16);
+}
 
 __device__ __forceinline__ i32x4 enc_rsrc(const void* base, uint32_t bytes) {
     const uint64_t p = reinterpret_cast<uint64_t>(base);
@@ -374,6 +241,11 @@ __device__ __forceinline__ uint2 lds_read_tr16(const char* p) {
     return __builtin_bit_cast(uint2, v);
 }
 
+// first stage of share q of ks over a width of w model columns
+__host__ __device__ inline int enc_stage(int w, int ks, int q) {
+    return static_cast<int>(static_cast<int64_t>(w / kEncK) * q / ks);
+}
+
 __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
     // one LDS object per ring slot, each named at compile time where it is read, so the wait
     // before a fragment read only covers the DMA into that slot
@@ -382,21 +254,24 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
     __shared__ __attribute__((aligned(1024))) char lds2[kEncStage];
     __shared__ __attribute__((aligned(1024))) char lds3[kEncStage];
     static_assert(kEncT * kEncRow == kEncK * kEncC * 2, "token rows and V rows fill equal halves of a stage");
-    const int ct_n = a.rw / kEncC, tt_n = a.h / kEncT;
-    const int n = ct_n * tt_n * a.slices;
+    const int ct_n = (a.rw + kEncC - 1) / kEncC, tt_n = (a.h + kEncT - 1) / kEncT;
+    const int n = ct_n * tt_n * a.ks * a.slices;
     const int g = blockIdx.x;
-    int ct, tts;
+    int ct, xt;  // column tile; (slice, token tile, share of the width)
     if (n % (8 * ct_n) == 0) {
-        // the column tiles of one token tile run on one XCD (workgroups go round-robin over the
+        // the column tiles of one block of X run on one XCD (workgroups go round-robin over the
         // eight): X rows are fetched into that XCD's L2 once for all of them
         const int q = g / 8;
         ct = q % ct_n;
-        tts = g % 8 + 8 * (q / ct_n);
+        xt = g % 8 + 8 * (q / ct_n);
     } else {
         ct = g % ct_n;
-        tts = g / ct_n;
+        xt = g / ct_n;
     }
+    const int kq = xt % a.ks, tts = xt / a.ks;
     const int s = tts / tt_n, tt = tts % tt_n;
+    const int valid = min(kEncT, a.h - tt * kEncT);  // tokens of this tile
+    const int st0 = enc_stage(a.w, a.ks, kq), ns = enc_stage(a.w, a.ks, kq + 1) - st0;
 
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
@@ -413,7 +288,7 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int t = tt * kEncT + utg * 8 + q;
-        rowv[q] = has_u && urg * 8 < a.rh ? ldg16(static_cast<const bf16_t*>(a.u) + static_cast<int64_t>(t) * a.rh + urg * 8)
+        rowv[q] = has_u && urg * 8 < a.rh && t < a.h ? ldg16(static_cast<const bf16_t*>(a.u) + static_cast<int64_t>(t) * a.rh + urg * 8)
                                            : make_uint4(0, 0, 0, 0);
     }
 
@@ -423,21 +298,26 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
     // chunk c of V row k sits at c ^ 2 (k % 4)); both swizzles are applied on the global side
     const bool tok_wave = wave < 4;
     const uint32_t vrow_bytes = static_cast<uint32_t>(a.rw) * 2u;
+    // (both bases start at this workgroup's first stage)
     const i32x4 rs = tok_wave
-        ? enc_rsrc(static_cast<const bf16_t*>(a.x) + (static_cast<int64_t>(s) * a.h + static_cast<int64_t>(tt) * kEncT) * a.w,
-                   kEncT * row_bytes)
-        : enc_rsrc(a.v, static_cast<uint32_t>(a.w) * vrow_bytes);
+        ? enc_rsrc(static_cast<const bf16_t*>(a.x) + (static_cast<int64_t>(s) * a.h + static_cast<int64_t>(tt) * kEncT) * a.w +
+                       st0 * kEncK,
+                   static_cast<uint32_t>(valid) * row_bytes - static_cast<uint32_t>(st0) * kEncRow)
+        : enc_rsrc(static_cast<const bf16_t*>(a.v) + static_cast<int64_t>(st0) * kEncK * a.rw,
+                   static_cast<uint32_t>(ns) * kEncK * vrow_bytes);
     const int sstep = tok_wave ? kEncRow : kEncK * static_cast<int>(vrow_bytes);  // bytes per stage
     uint32_t voff[kEncLoads];
 #pragma unroll
     for (int j = 0; j < kEncLoads; ++j) {
         if (tok_wave) {
+            // rows past the last token repeat it (their products are dropped below)
             const int row = 16 * wave + 4 * j + (lane >> 4);
-            voff[j] = static_cast<uint32_t>(row) * row_bytes + static_cast<uint32_t>(((lane & 15) ^ (row & 15)) * 16);
+            voff[j] = static_cast<uint32_t>(min(row, valid - 1)) * row_bytes + static_cast<uint32_t>(((lane & 15) ^ (row & 15)) * 16);
         } else {
+            // columns past r_w repeat its last eight (not stored)
             const int k = 32 * (wave - 4) + 8 * j + (lane >> 3);
-            voff[j] = static_cast<uint32_t>(k) * vrow_bytes + static_cast<uint32_t>(ct * kEncC * 2) +
-                      static_cast<uint32_t>(((lane & 7) ^ (2 * (k & 3))) * 16);
+            const int col = min(ct * kEncC + ((lane & 7) ^ (2 * (k & 3))) * 8, a.rw - 8);
+            voff[j] = static_cast<uint32_t>(k) * vrow_bytes + static_cast<uint32_t>(col * 2);
         }
     }
     auto issue = [&](int st, char* slot) {
@@ -448,31 +328,36 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
                                 static_cast<int>(voff[j]), st * sstep, 0, 0);
     };
 
-    // fragments: A = column 32 wn + l32 of P (V's column ct * 64 + 32 wn + l32), model columns
-    // 16 (2 q + kh) + 8 lh .. + 7 of the stage in k-step q; B = token row 32 wm + l32, the 16
-    // bytes of logical chunk 2 (2 q + kh) + lh. A transposing read by the 16 lanes of a group
-    // (g = lane / 16, i = lane % 16) takes 8 bytes from V row k0 + i / 4 at columns
-    // mb + 4 (i % 4) .. + 3 and hands lane i the 4 rows k0 .. k0 + 3 of column mb + i; here
-    // k0 = 16 (2 q + kh) + 8 (g / 2) + 4 h for the halves h = 0, 1 of the lane's 8 model columns
-    // and mb = 32 wn + 16 (g % 2), so lane l gets column 32 wn + l % 32 as the product needs
-    const int wm = wave & 1, wn = (wave >> 1) & 1, kh = wave >> 2;
-    const int rb = 32 * wm + l32;
+    // Wave w takes k-step w of every stage (16 model columns) for the whole 64 x 64 tile: an
+    // operand fragment is read from LDS once and used by two products, and the eight float32
+    // chains of an element are an eighth of the share of the width long.
+    // Fragments: A = column 32 wn + l32 of P (V's column ct * 64 + 32 wn + l32), model columns
+    // 16 w + 8 lh .. + 7 of the stage; B = token row 32 wm + l32, the 16 bytes of logical chunk
+    // 2 w + lh. A transposing read by the 16 lanes of a group (g = lane / 16, i = lane % 16)
+    // takes 8 bytes from V row k0 + i / 4 at columns mb + 4 (i % 4) .. + 3 and hands lane i the
+    // 4 rows k0 .. k0 + 3 of column mb + i; here k0 = 16 w + 8 (g / 2) + 4 h for the halves
+    // h = 0, 1 of the lane's 8 model columns and mb = 32 wn + 16 (g % 2), so lane l gets column
+    // 32 wn + l % 32 as the product needs
     const int gi = lane & 15, gg = lane >> 4;
-    const int chv = 4 * wn + 2 * (gg & 1) + ((gi & 3) >> 1);  // 16-byte chunk of the V row
-    const int offv = kEncT * kEncRow + ((chv ^ (2 * (gi >> 2))) * 16) + (gi & 1) * 8;
-    int offa[4][2], offb[4];
+    int offa[2][2], offb[2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int ch = 2 * (2 * q + kh) + lh;
+    for (int wn = 0; wn < 2; ++wn) {
+        const int chv = 4 * wn + 2 * (gg & 1) + ((gi & 3) >> 1);  // 16-byte chunk of the V row
+        const int offv = kEncT * kEncRow + ((chv ^ (2 * (gi >> 2))) * 16) + (gi & 1) * 8;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) offa[q][h] = offv + (16 * (2 * q + kh) + 8 * (gg >> 1) + 4 * h + (gi >> 2)) * 128;
-        offb[q] = rb * kEncRow + ((ch ^ (rb & 15)) * 16);
+        for (int h = 0; h < 2; ++h) offa[wn][h] = offv + (16 * wave + 8 * (gg >> 1) + 4 * h + (gi >> 2)) * 128;
     }
-    f32x16 acc;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int wm = 0; wm < 2; ++wm) {
+        const int rb = 32 * wm + l32;
+        offb[wm] = rb * kEncRow + (((2 * wave + lh) ^ (rb & 15)) * 16);
+    }
+    f32x16 acc[2][2];  // [wn][wm]
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b >> 1][b & 1][r] = 0.f;
 
-    const int ns = a.w / kEncK;
     auto step = [&](int st, const char* cur, char* refill) {
         if (st >= ns) return;
         const int later = min(kEncRing - 2, ns - 1 - st);  // stages issued after this one
@@ -486,17 +371,19 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         if (st + kEncRing - 1 < ns) issue(st + kEncRing - 1, refill);
-        uint4 fa[4], fb[4];
+        uint4 fa[2], fb[2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint2 lo = lds_read_tr16(cur + offa[q][0]), hi = lds_read_tr16(cur + offa[q][1]);
-            fa[q] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            fb[q] = *reinterpret_cast<const uint4*>(cur + offb[q]);
+        for (int i = 0; i < 2; ++i) {
+            const uint2 lo = lds_read_tr16(cur + offa[i][0]), hi = lds_read_tr16(cur + offa[i][1]);
+            fa[i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            fb[i] = *reinterpret_cast<const uint4*>(cur + offb[i]);
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[q]), __builtin_bit_cast(bf16x8, fb[q]),
-                                                          acc, 0, 0, 0);
+        for (int wn = 0; wn < 2; ++wn)
+#pragma unroll
+            for (int wm = 0; wm < 2; ++wm)
+                acc[wn][wm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[wn]),
+                                                                      __builtin_bit_cast(bf16x8, fb[wm]), acc[wn][wm], 0, 0, 0);
     };
     if (ns > 0) issue(0, lds0);
     if (ns > 1) issue(1, lds1);
@@ -508,34 +395,56 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
         step(st + 3, lds3, lds2);
     }
 
-    // the odd-step half of each block is added to the even-step half
+    // the eight waves' sums of each element through LDS, 16 KB a wave: [block][register / 4][lane]
     __syncthreads();
-    float* red = reinterpret_cast<float*>(lds0);
-    if (kh == 1) {
+    char* const ring[4] = {lds0, lds1, lds2, lds3};
 #pragma unroll
-        for (int r = 0; r < 16; ++r) red[((wave - 4) * 16 + r) * 64 + lane] = acc[r];
+    for (int i = 0; i < 4; ++i) {
+        if ((wave >> 1) != i) continue;
+        f32x4* mine = reinterpret_cast<f32x4*>(ring[i]) + (wave & 1) * 1024;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = acc[b >> 1][b & 1][4 * q + e];
+                mine[(b * 4 + q) * 64 + lane] = v;
+            }
+    }
+    __syncthreads();
+    // wave w sums registers 8 (w % 2) .. + 7 of block w / 2, pairwise over the waves
+    const int blk = wave >> 1, wm = blk & 1, wn = blk >> 1;
+    f32x4 sum[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        f32x4 v[8];
+#pragma unroll
+        for (int p = 0; p < 8; ++p)
+            v[p] = reinterpret_cast<const f32x4*>(ring[p >> 1])[(p & 1) * 1024 + (blk * 4 + 2 * (wave & 1) + q) * 64 + lane];
+        sum[q] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     }
     char* lds_u = lds1;  // U^T [r][64 tokens], 128-byte rows (32 KB)
     char* lds_p = lds2;  // P^T planes [3][64 columns][64 tokens] (24 KB)
     __syncthreads();
-    if (kh == 0) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] += red[(wave * 16 + r) * 64 + lane];
+    {
         // lane holds token j = 32 wm + l32 and, in register r, column i = 32 wn + 8 (r / 4) + 4 lh + r % 4
         const int j = 32 * wm + l32;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = 32 * wn + 8 * (r / 4) + 4 * lh + (r % 4);
-            const float v = acc[r];
-            const uint16_t hi = f32_to_bf16(v);
-            const float r1 = v - bf16_to_f32(hi);
-            const uint16_t mid = f32_to_bf16(r1);
-            const uint16_t lo = f32_to_bf16(r1 - bf16_to_f32(mid));
-            const int off = i * 128 + (((j >> 3) ^ ((i >> 1) & 7)) * 16) + (j & 7) * 2;
-            *reinterpret_cast<uint16_t*>(lds_p + 0 * kEncC * 128 + off) = hi;
-            *reinterpret_cast<uint16_t*>(lds_p + 1 * kEncC * 128 + off) = mid;
-            *reinterpret_cast<uint16_t*>(lds_p + 2 * kEncC * 128 + off) = lo;
-        }
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = 32 * wn + 8 * (2 * (wave & 1) + q) + 4 * lh + e;
+                const float v = j < valid ? sum[q][e] : 0.f;
+                const uint16_t hi = f32_to_bf16(v);
+                const float r1 = v - bf16_to_f32(hi);
+                const uint16_t mid = f32_to_bf16(r1);
+                const uint16_t lo = f32_to_bf16(r1 - bf16_to_f32(mid));
+                const int off = i * 128 + (((j >> 3) ^ ((i >> 1) & 7)) * 16) + (j & 7) * 2;
+                *reinterpret_cast<uint16_t*>(lds_p + 0 * kEncC * 128 + off) = hi;
+                *reinterpret_cast<uint16_t*>(lds_p + 1 * kEncC * 128 + off) = mid;
+                *reinterpret_cast<uint16_t*>(lds_p + 2 * kEncC * 128 + off) = lo;
+            }
     }
     if (has_u) {
         const int r0 = urg * 8;
@@ -573,14 +482,14 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
                 z[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ua[i]), __builtin_bit_cast(bf16x8, pb[pl]),
                                                                z[i], 0, 0, 0);
     }
-    float* part = a.part + (static_cast<int64_t>(s) * tt_n + tt) * a.rh * a.rw;
+    float* part = a.part + static_cast<int64_t>(xt) * a.rh * a.rw;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int r = rbase + 32 * i + 8 * (q / 4) + 4 * lh + (q % 4);
             const int c = ct * kEncC + 32 * cb + l32;
-            if (r < a.rh) part[static_cast<int64_t>(r) * a.rw + c] = z[i][q];
+            if (r < a.rh && c < a.rw) part[static_cast<int64_t>(r) * a.rw + c] = z[i][q];
         }
 }
 
@@ -1075,14 +984,12 @@ hipError_t launch_transpose(DType dt, const void* src, int rows, int cols, void*
     return hipGetLastError();
 }
 
-hipError_t launch_utp(DType udt, const UtpArgs& g, hipStream_t s) {
+hipError_t launch_utp(const UtpArgs& g, hipStream_t s) {
     const int chunks = (g.T + g.tc - 1) / g.tc;
     dim3 grid((g.rw + kUtpC - 1) / kUtpC, chunks, g.slices);
-    static_assert(kUtpC == kU3C, "both contractions tile P by the same column blocks");
     {
         ProfileScope prof("codec_utp", s);
-        if (udt == DType::BF16) hipLaunchKernelGGL(utp3_kernel, grid, dim3(256), 0, s, g);
-        else hipLaunchKernelGGL(utp_kernel<float>, grid, dim3(256), 0, s, g);
+        hipLaunchKernelGGL(utp_kernel<float>, grid, dim3(256), 0, s, g);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1093,15 +1000,24 @@ hipError_t launch_utp(DType udt, const UtpArgs& g, hipStream_t s) {
     return hipGetLastError();
 }
 
-bool encode_fused_ok(DType dt, int h, int w, int rh, int rw) {
-    return dt == DType::BF16 && h > 0 && h % kEncT == 0 && rw % kEncC == 0 && w % kEncK == 0 && rh <= 256;
+int encode_splits(int h, int w, int rw, int slices) {
+    // Shares of the width while the tiles number at most half the CUs, of at least two stages
+    // each. 128 workgroups, not 256: the partial sums that a further halving adds cost what it
+    // saves (1000 x 2048 ranks 128: 13.4 us with 4 shares, 16.4 with 8, 26 with 16; 2047 x 4096
+    // ranks 256: 23.0 us with 1 share, 22.4 with 2; ranks 16: 13.4 us with 4, 14.8 with 8).
+    const int64_t tiles = std::max<int64_t>(1, static_cast<int64_t>((rw + kEncC - 1) / kEncC) * ((h + kEncT - 1) / kEncT) * slices);
+    const int ns = w / kEncK;
+    int64_t ks = std::max<int64_t>(1, std::min<int64_t>(128 / tiles, ns / 2));
+    // a share of V stays below 2 GiB (the offsets of its buffer loads)
+    while ((static_cast<int64_t>(ns) / ks + 1) * kEncK * rw * 2 >= (int64_t(1) << 31)) ++ks;
+    return static_cast<int>(ks);
 }
 
 hipError_t launch_encode_fused(const EncArgs& a, float* z, hipStream_t s) {
-    const int tt_n = a.h / kEncT;
+    const int tt_n = ((a.h + kEncT - 1) / kEncT) * a.ks;
     {
         ProfileScope prof("codec_encode", s);
-        hipLaunchKernelGGL(encode_fused_kernel, dim3((a.rw / kEncC) * tt_n * a.slices), dim3(512), 0, s, a);
+        hipLaunchKernelGGL(encode_fused_kernel, dim3(((a.rw + kEncC - 1) / kEncC) * tt_n * a.slices), dim3(512), 0, s, a);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -69,8 +69,8 @@ hipError_t launch_transpose(DType dt, const void* src, int rows, int cols, void*
 
 // Z[s][r][c] = sum_t U[t][r] P[s][t][c] (r < rh, c < rw, t < T, s < slices): float32
 // partial sums over token chunks of tc rows go to part ([slices][ceil(T / tc)][rh][rw]
-// float32), then are added in chunk order into z ([slices][rh][rw]; deterministic). U has
-// the layer dtype, P and Z are float32. rh <= 256; rh and rw are multiples of 16; every row
+// float32), then are added in chunk order into z ([slices][rh][rw]; deterministic). U, P
+// and Z are float32. rh <= 256; rh and rw are multiples of 16; every row
 // is 16-byte aligned.
 struct UtpArgs {
     const void* u;
@@ -79,18 +79,19 @@ struct UtpArgs {
     float* part;
     float* z;
 };
-hipError_t launch_utp(DType udt, const UtpArgs& g, hipStream_t s);
-// Fused encoder of bf16 layers: part[s][tt][r][c] = U^T (X V) over 64-token tiles tt (X [slices][h][w],
-// V [w][r_w], U [h][r_h]), then z[s] = sum over tt in order. Applies when encode_fused_ok();
-// part holds slices * (h / 64) * r_h * r_w floats.
+hipError_t launch_utp(const UtpArgs& g, hipStream_t s);
+// Fused encoder of bf16 layers: part[s][tt][kq][r][c] = U^T (X V) over 64-token tiles tt and
+// ks = encode_splits() shares kq of the width (X [slices][h][w], V [w][r_w], U [h][r_h]; w a multiple
+// of 128), then z[s] = the sum over tt and kq in order. part holds slices * ceil(h / 64) * ks * r_h * r_w floats.
 struct EncArgs {
     const void* x;   // bf16
     const void* v;   // bf16
     const void* u;   // bf16
     float* part;
     int h, w, rh, rw, slices;
+    int ks;          // shares of the width: encode_splits()
 };
-bool encode_fused_ok(DType dt, int h, int w, int rh, int rw);
+int encode_splits(int h, int w, int rw, int slices);
 // Small batches (h <= 64 tokens per slice, r_h <= 64): the encoder in two launches through
 // part (codec_small_part_floats floats) and the decoder in one, in float32 throughout.
 bool codec_small_ok(int h, int w, int rh, int rw);

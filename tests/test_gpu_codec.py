@@ -47,7 +47,7 @@ def test_full_rank_codec_round_trips_on_gpu():
     (4, 256, 768, 64, 64, W.BF16),   # the paper-shaped layers: 4 sequences of 256 tokens
     (1, 300, 256, 80, 64, W.BF16),   # r_h ending inside the second 64-row block of U^T P
     (2, 260, 128, 208, 112, W.F32),  # ... inside the fourth
-    # bf16 layers of whole 64-token, 64-column tiles take the fused encoder:
+    # bf16 layers take the fused encoder, here in whole 64-token, 64-column tiles:
     (3, 128, 256, 80, 128, W.BF16),   # r_h inside the second 64-row block, two column tiles
     (2, 256, 384, 256, 192, W.BF16),  # three column tiles of a token tile placed on one XCD
     (17, 128, 128, 16, 64, W.BF16),   # two tiles per slice, more slices than one batch
@@ -55,6 +55,10 @@ def test_full_rank_codec_round_trips_on_gpu():
     (1, 128, 128, 128, 64, W.BF16),    # one band of two 64-column chunks
     (1, 256, 512, 256, 128, W.BF16),   # with the fused encoder
     (1, 4096, 2176, 128, 64, W.BF16),  # runs of three chunks, the last of each band one chunk (34 chunks)
+    # ... with a last tile of one token or column block, and the width in shares of unequal stages:
+    (1, 65, 1152, 64, 16, W.BF16),     # 9 stages in 4 shares, one token in the second tile
+    (1, 127, 128, 16, 80, W.BF16),     # one stage
+    (2, 1000, 640, 144, 208, W.BF16),  # tiles that fill the machine: one share
     # at most 64 tokens per slice take the small-batch encoder and decoder:
     (3, 48, 256, 32, 48, W.BF16),
     (2, 64, 256, 64, 256, W.F32),     # the largest r_h and r_w of that path

@@ -164,9 +164,9 @@ struct CodecWs {
     bool fused;  // bf16 layers: P and U^T P in one kernel
     int ks;      // its shares of the width
     bool small;  // at most 64 tokens per slice: the small-batch encoder and decoder
-    // decode: Z rounded to the layer dtype (bf16 only), W = V_hat Z^T per slice, and the segment
-    // offsets and row maps of the grouped products over a batch of slices
-    size_t zb, wt, seg_w, rows_w, seg_h, rows_h, dec_total;
+    // decode: W = V_hat Z^T per slice; float32 layers: the segment offsets and row maps of the
+    // grouped products over a batch of slices
+    size_t wt, seg_w, rows_w, seg_h, rows_h, dec_total;
 };
 
 // Slices coded by one set of launches: at most 16, and few enough that a batch of X stays
@@ -209,14 +209,12 @@ CodecWs codec_ws(const ec2moe_codec_desc* d) {
                  : up(nb * chunks * d->r_h * d->r_w * 4);
     w.enc_total = o;
     o = shared;
-    // Z rounded to bf16 ahead of the decoder's GEMM, where the one-launch product does not apply
-    const bool vzt = vzt_ok(static_cast<DType>(d->dtype), d->w, d->r_h, d->r_w);
-    w.zb = o; o += vzt ? 0 : up(nb * d->r_h * d->r_w * eb);
-    w.wt = o; o += up(nb * d->w * d->r_h * eb);
-    w.seg_w = o; o += up((nb + 1) * 4);
-    w.rows_w = o; o += up(nb * d->w * 4);
-    w.seg_h = o; o += up((nb + 1) * 4);
-    w.rows_h = o; o += up(nb * std::max(1, d->h) * 4);
+    const bool bf16 = d->dtype == EC2MOE_BF16;
+    w.wt = o; o += up(nb * d->w * (bf16 ? expand_rank(d->r_h) : d->r_h) * eb);
+    w.seg_w = o; o += bf16 ? 0 : up((nb + 1) * 4);
+    w.rows_w = o; o += bf16 ? 0 : up(nb * d->w * 4);
+    w.seg_h = o; o += bf16 ? 0 : up((nb + 1) * 4);
+    w.rows_h = o; o += bf16 ? 0 : up(nb * std::max(1, d->h) * 4);
     w.dec_total = o;
     return w;
 }
@@ -593,30 +591,26 @@ ec2moe_status ec2moe_lowrank_decode(const ec2moe_codec_desc* desc, const float* 
         }
         return hip_status(e, "lowrank_decode launch");
     }
+    if (dt == DType::BF16) {
+        // Z is rounded to bf16 first (the product runs on the bf16 matrix cores; Wt itself is
+        // rounded to bf16 anyway)
+        const size_t slice_bytes = static_cast<size_t>(desc->h) * desc->w * eb;
+        for (int c0 = 0; c0 < desc->n_slices && e == hipSuccess; c0 += w.batch) {
+            const int nc = std::min(w.batch, desc->n_slices - c0);
+            e = launch_decode_bf16(z + static_cast<size_t>(c0) * zn, u_hat, v_hat, desc->h, desc->w, desc->r_h,
+                                   desc->r_w, nc, wt, static_cast<char*>(x_hat) + c0 * slice_bytes, stream);
+        }
+        return hip_status(e, "lowrank_decode launch");
+    }
     if (desc->n_slices == 1) {
         // Wt = V_hat Z^T  [w][r_h]: both operands are K-contiguous rows (V_hat [w][r_w], Z [r_h][r_w]).
-        // In bf16 layers Z is rounded to bf16 first (the product runs on the bf16 matrix cores;
-        // Wt itself is rounded to bf16 anyway), inside the one-launch product where the shape allows.
-        if (vzt_ok(dt, desc->w, desc->r_h, desc->r_w)) {
-            e = launch_vzt(z, v_hat, desc->w, desc->r_h, desc->r_w, 1, wt, stream);
-        } else {
-            const void* zop = z;
-            if (dt == DType::BF16) {
-                e = launch_f32_to_bf16(z, zn, at<void>(ws, w.zb), stream);
-                zop = at<void>(ws, w.zb);
-            }
-            if (e == hipSuccess) {
-                GemmArgs gw{};
-                gw.tok = v_hat; gw.row_index = nullptr; gw.w = zop; gw.w_group_stride = 0; gw.seg = nullptr;
-                gw.n_groups = 1; gw.rows = desc->w; gw.K = desc->r_w; gw.N = desc->r_h; gw.out = wt; gw.ldo = desc->r_h;
-                gw.name = "codec_vzt";
-                gw.src_rows = desc->w; gw.w_rows = desc->r_h; gw.part = at<float>(ws, w.gpart); gw.max_split = kMaxSplit;
-                e = launch_gemm(dt, Epilogue::Store, OutType::Same, gw, stream);
-            }
-        }
-        if (e == hipSuccess && expand_ok(dt, desc->h, desc->w, desc->r_h)) {
-            e = launch_expand(u_hat, wt, desc->h, desc->w, desc->r_h, x_hat, stream);
-        } else if (e == hipSuccess) {
+        GemmArgs gw{};
+        gw.tok = v_hat; gw.row_index = nullptr; gw.w = z; gw.w_group_stride = 0; gw.seg = nullptr;
+        gw.n_groups = 1; gw.rows = desc->w; gw.K = desc->r_w; gw.N = desc->r_h; gw.out = wt; gw.ldo = desc->r_h;
+        gw.name = "codec_vzt";
+        gw.src_rows = desc->w; gw.w_rows = desc->r_h; gw.part = at<float>(ws, w.gpart); gw.max_split = kMaxSplit;
+        e = launch_gemm(dt, Epilogue::Store, OutType::Same, gw, stream);
+        if (e == hipSuccess) {
             // X_hat = U_hat Wt^T  [h][w]
             GemmArgs g{};
             g.tok = u_hat; g.row_index = nullptr; g.w = wt; g.w_group_stride = 0; g.seg = nullptr; g.n_groups = 1;
@@ -635,21 +629,15 @@ ec2moe_status ec2moe_lowrank_decode(const ec2moe_codec_desc* desc, const float* 
     for (int c0 = 0; c0 < desc->n_slices && e == hipSuccess; c0 += w.batch) {
         const int nc = std::min(w.batch, desc->n_slices - c0);
         const float* zc = z + static_cast<size_t>(c0) * zn;
-        const bool vzt = vzt_ok(dt, desc->w, desc->r_h, desc->r_w);
-        void* zb = dt == DType::BF16 && !vzt ? at<void>(ws, w.zb) : nullptr;
-        e = launch_codec_prep(zc, nc * zn, zb, nc, desc->w, desc->h, seg_w, rows_w, seg_h, rows_h, stream);
+        e = launch_codec_prep(nc, desc->w, desc->h, seg_w, rows_w, seg_h, rows_h, stream);
         if (e != hipSuccess) break;
         // Wt[s] = V_hat Z[s]^T  [w][r_h]
-        if (vzt) {
-            e = launch_vzt(zc, v_hat, desc->w, desc->r_h, desc->r_w, nc, wt, stream);
-        } else {
-            GemmArgs gw{};
-            gw.tok = v_hat; gw.row_index = rows_w; gw.w = zb ? zb : static_cast<const void*>(zc);
-            gw.w_group_stride = zn; gw.seg = seg_w; gw.n_groups = nc; gw.rows = int64_t(nc) * desc->w;
-            gw.K = desc->r_w; gw.N = desc->r_h; gw.out = wt; gw.ldo = desc->r_h; gw.name = "codec_vzt";
-            gw.src_rows = desc->w; gw.w_rows = desc->r_h; gw.part = at<float>(ws, w.gpart); gw.max_split = kMaxSplit;
-            e = launch_gemm(dt, Epilogue::Store, OutType::Same, gw, stream);
-        }
+        GemmArgs gw{};
+        gw.tok = v_hat; gw.row_index = rows_w; gw.w = zc;
+        gw.w_group_stride = zn; gw.seg = seg_w; gw.n_groups = nc; gw.rows = int64_t(nc) * desc->w;
+        gw.K = desc->r_w; gw.N = desc->r_h; gw.out = wt; gw.ldo = desc->r_h; gw.name = "codec_vzt";
+        gw.src_rows = desc->w; gw.w_rows = desc->r_h; gw.part = at<float>(ws, w.gpart); gw.max_split = kMaxSplit;
+        e = launch_gemm(dt, Epilogue::Store, OutType::Same, gw, stream);
         if (e != hipSuccess) break;
         // X_hat[s] = U_hat Wt[s]^T  [h][w]
         GemmArgs g{};

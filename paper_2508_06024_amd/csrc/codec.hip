@@ -182,8 +182,8 @@ __global__ __launch_bounds__(256) void utp_kernel(UtpArgs g) {
 // for those model columns, 128 bytes each: the tile's 64 columns) filled by buffer_load ... lds,
 // so three stages are in flight while one is consumed. V's operand fragments need 8 consecutive
 // model columns per lane, which run down the staged rows: the gfx950 transposing LDS read
-// (ds_read_b64_tr_b16) gathers them, 4 rows at a time. Eight waves, one k-step of every stage
-// each; their sums meet in LDS. The P tile is then split exactly into three bf16 planes, p = hi +
+// (ds_read_b64_tr_b16) gathers them, 4 rows at a time. Eight waves, two k-steps of every stage
+// for half the tokens each; their sums meet in LDS. The P tile is then split exactly into three bf16 planes, p = hi +
 // mid + lo up to 2^-27 |p| (hi = bf16(p), mid = bf16(p - hi), lo = bf16(p - hi - mid); each
 // difference is exact in float32), whose products with U are exact in float32: the accuracy of a
 // float32 contraction at 3/16 of its matrix-core cost. U^T [r][t] (an 8x8 register transpose of
@@ -328,31 +328,34 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
                                 static_cast<int>(voff[j]), st * sstep, 0, 0);
     };
 
-    // Wave w takes k-step w of every stage (16 model columns) for the whole 64 x 64 tile: an
-    // operand fragment is read from LDS once and used by two products, and the eight float32
-    // chains of an element are an eighth of the share of the width long.
+    // Wave w takes k-steps 2 kp and 2 kp + 1 (kp = w / 2, 16 model columns each) of every stage
+    // for the tile's 64 columns and tokens 32 wm .. + 31 (wm = w % 2): a token fragment read from
+    // LDS serves two products. Each k-step has its own accumulators: an element's eight float32
+    // chains are an eighth of the share of the width long.
     // Fragments: A = column 32 wn + l32 of P (V's column ct * 64 + 32 wn + l32), model columns
-    // 16 w + 8 lh .. + 7 of the stage; B = token row 32 wm + l32, the 16 bytes of logical chunk
-    // 2 w + lh. A transposing read by the 16 lanes of a group (g = lane / 16, i = lane % 16)
-    // takes 8 bytes from V row k0 + i / 4 at columns mb + 4 (i % 4) .. + 3 and hands lane i the
-    // 4 rows k0 .. k0 + 3 of column mb + i; here k0 = 16 w + 8 (g / 2) + 4 h for the halves
-    // h = 0, 1 of the lane's 8 model columns and mb = 32 wn + 16 (g % 2), so lane l gets column
-    // 32 wn + l % 32 as the product needs
+    // 16 k + 8 lh .. + 7 of the stage in k-step k; B = token row 32 wm + l32, the 16 bytes of
+    // logical chunk 2 k + lh. A transposing read by the 16 lanes of a group (g = lane / 16,
+    // i = lane % 16) takes 8 bytes from V row k0 + i / 4 at columns mb + 4 (i % 4) .. + 3 and
+    // hands lane i the 4 rows k0 .. k0 + 3 of column mb + i; here k0 = 16 k + 8 (g / 2) + 4 h for
+    // the halves h = 0, 1 of the lane's 8 model columns and mb = 32 wn + 16 (g % 2), so lane l
+    // gets column 32 wn + l % 32 as the product needs
+    const int wm = wave & 1, kp = wave >> 1;
     const int gi = lane & 15, gg = lane >> 4;
-    int offa[2][2], offb[2];
+    int offa[2][2][2], offb[2];  // [k-step][wn][half], [k-step]
 #pragma unroll
-    for (int wn = 0; wn < 2; ++wn) {
-        const int chv = 4 * wn + 2 * (gg & 1) + ((gi & 3) >> 1);  // 16-byte chunk of the V row
-        const int offv = kEncT * kEncRow + ((chv ^ (2 * (gi >> 2))) * 16) + (gi & 1) * 8;
+    for (int q = 0; q < 2; ++q) {
+        const int k = 2 * kp + q;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) offa[wn][h] = offv + (16 * wave + 8 * (gg >> 1) + 4 * h + (gi >> 2)) * 128;
-    }
+        for (int wn = 0; wn < 2; ++wn) {
+            const int chv = 4 * wn + 2 * (gg & 1) + ((gi & 3) >> 1);  // 16-byte chunk of the V row
+            const int offv = kEncT * kEncRow + ((chv ^ (2 * (gi >> 2))) * 16) + (gi & 1) * 8;
 #pragma unroll
-    for (int wm = 0; wm < 2; ++wm) {
+            for (int h = 0; h < 2; ++h) offa[q][wn][h] = offv + (16 * k + 8 * (gg >> 1) + 4 * h + (gi >> 2)) * 128;
+        }
         const int rb = 32 * wm + l32;
-        offb[wm] = rb * kEncRow + (((2 * wave + lh) ^ (rb & 15)) * 16);
+        offb[q] = rb * kEncRow + (((2 * k + lh) ^ (rb & 15)) * 16);
     }
-    f32x16 acc[2][2];  // [wn][wm]
+    f32x16 acc[2][2];  // [k-step][wn]
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -371,19 +374,22 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         if (st + kEncRing - 1 < ns) issue(st + kEncRing - 1, refill);
-        uint4 fa[2], fb[2];
+        uint4 fa[2][2], fb[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint2 lo = lds_read_tr16(cur + offa[i][0]), hi = lds_read_tr16(cur + offa[i][1]);
-            fa[i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            fb[i] = *reinterpret_cast<const uint4*>(cur + offb[i]);
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int wn = 0; wn < 2; ++wn) {
+                const uint2 lo = lds_read_tr16(cur + offa[q][wn][0]), hi = lds_read_tr16(cur + offa[q][wn][1]);
+                fa[q][wn] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+            fb[q] = *reinterpret_cast<const uint4*>(cur + offb[q]);
         }
 #pragma unroll
-        for (int wn = 0; wn < 2; ++wn)
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
-            for (int wm = 0; wm < 2; ++wm)
-                acc[wn][wm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[wn]),
-                                                                      __builtin_bit_cast(bf16x8, fb[wm]), acc[wn][wm], 0, 0, 0);
+            for (int wn = 0; wn < 2; ++wn)
+                acc[q][wn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[q][wn]),
+                                                                     __builtin_bit_cast(bf16x8, fb[q]), acc[q][wn], 0, 0, 0);
     };
     if (ns > 0) issue(0, lds0);
     if (ns > 1) issue(1, lds1);
@@ -395,34 +401,34 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
         step(st + 3, lds3, lds2);
     }
 
-    // the eight waves' sums of each element through LDS, 16 KB a wave: [block][register / 4][lane]
+    // the four k-pairs' sums of each element through LDS, 8 KB a wave (those of a pair in one
+    // ring slot): [wm][wn][register / 4][lane]
     __syncthreads();
     char* const ring[4] = {lds0, lds1, lds2, lds3};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        if ((wave >> 1) != i) continue;
-        f32x4* mine = reinterpret_cast<f32x4*>(ring[i]) + (wave & 1) * 1024;
+        if (kp != i) continue;
+        f32x4* mine = reinterpret_cast<f32x4*>(ring[i]) + wm * 512;
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int wn = 0; wn < 2; ++wn)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 f32x4 v;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[b >> 1][b & 1][4 * q + e];
-                mine[(b * 4 + q) * 64 + lane] = v;
+                for (int e = 0; e < 4; ++e) v[e] = acc[0][wn][4 * q + e] + acc[1][wn][4 * q + e];
+                mine[(wn * 4 + q) * 64 + lane] = v;
             }
     }
     __syncthreads();
-    // wave w sums registers 8 (w % 2) .. + 7 of block w / 2, pairwise over the waves
-    const int blk = wave >> 1, wm = blk & 1, wn = blk >> 1;
+    // wave w sums registers 8 (kp % 2) .. + 7 of block (wm, wn = kp / 2) over the pairs
+    const int wn = kp >> 1, qh = 2 * (kp & 1);
     f32x4 sum[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        f32x4 v[8];
+        f32x4 v[4];
 #pragma unroll
-        for (int p = 0; p < 8; ++p)
-            v[p] = reinterpret_cast<const f32x4*>(ring[p >> 1])[(p & 1) * 1024 + (blk * 4 + 2 * (wave & 1) + q) * 64 + lane];
-        sum[q] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        for (int p = 0; p < 4; ++p) v[p] = reinterpret_cast<const f32x4*>(ring[p])[wm * 512 + (wn * 4 + qh + q) * 64 + lane];
+        sum[q] = (v[0] + v[1]) + (v[2] + v[3]);
     }
     char* lds_u = lds1;  // U^T [r][64 tokens], 128-byte rows (32 KB)
     char* lds_p = lds2;  // P^T planes [3][64 columns][64 tokens] (24 KB)
@@ -434,7 +440,7 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
         for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int i = 32 * wn + 8 * (2 * (wave & 1) + q) + 4 * lh + e;
+                const int i = 32 * wn + 8 * (qh + q) + 4 * lh + e;
                 const float v = j < valid ? sum[q][e] : 0.f;
                 const uint16_t hi = f32_to_bf16(v);
                 const float r1 = v - bf16_to_f32(hi);
@@ -650,14 +656,14 @@ __global__ __launch_bounds__(256) void dec_small_kernel(const float* __restrict_
 
 // ------------------------------------------------------------------ decoder, X_hat = U_hat Wt^T (bf16)
 //
-// X_hat[t][j] = sum_i U_hat[t][i] Wt[j][i] over K = r_h (128 or 256), rounded to bfloat16: a
-// rank-r_h expansion whose cost is its 2-byte output. A workgroup owns a band of 128 tokens and a
-// run of 64-column chunks of X_hat. Each of its four waves holds the U_hat operand fragments of its
-// 32 tokens in registers for the whole run; the chunks' Wt rows (64 x r_h, K-contiguous) stream
-// through two LDS buffers by buffer_load ... lds. A chunk's results wait in registers (packed to
-// bf16) and are stored after the next chunk's loads have landed, so the stores drain during that
-// chunk's products instead of under the wait for its loads (the wait is vmcnt(0): loads and stores
-// are not counted in order with each other). Two workgroups per CU overlap each other's waits.
+// X_hat[s][t][j] = sum_i U_hat[t][i] Wt[s][j][i] over K = r_h (Wt's rows are zero from r_h to RH),
+// rounded to bfloat16: a rank-r_h expansion whose cost is its 2-byte output. A workgroup owns a
+// band of 128 tokens and a run of 64-column chunks of one slice of X_hat. Each of its four waves
+// holds the U_hat operand fragments of its 32 tokens in registers for the whole run; the chunks'
+// Wt rows (64 x RH, K-contiguous) stream through two LDS buffers by buffer_load ... lds. A chunk's
+// results wait in registers (packed to bf16) and are stored behind the issue of the loads of the
+// chunk after the next, and the wait for those loads leaves the stores in flight (loads and stores
+// leave vmcnt in the order of their issue). Two workgroups per CU overlap each other's waits.
 // Wt is the A operand of v_mfma_f32_16x16x32_bf16 with its rows permuted: operand row m = 4 g + e
 // of block b is column 16 g + 4 b + e of the chunk, so a lane's 16 results of one token are 16
 // consecutive columns. Each wave passes its 32 x 64 results through 4 KB of LDS so that every
@@ -665,14 +671,28 @@ __global__ __launch_bounds__(256) void dec_small_kernel(const float* __restrict_
 // instruction: 8% slower). Staged Wt row R keeps its 16-byte chunk c at c ^ ex_swz(R), which
 // spreads the 16 rows read by one group of lanes over distinct banks; the output staging keeps
 // piece p of row r at p ^ (r % 8).
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 constexpr int kExT = 128;  // tokens per band: four waves of 32
 constexpr int kExC = 64;   // columns of X_hat per chunk
+// largest r_w of the fused form (0: none)
+constexpr int ex_fused_rw(int rp) { return rp <= 64 ? 256 : rp <= 128 ? 128 : 0; }
 
-__device__ __forceinline__ int ex_swz(int r) { return (r & 3) | (((r >> 4) & 3) << 2); }
-
+// The 16 rows that a group of lanes reads differ in bits 0, 1, 4 and 5; together with the place of
+// the row inside 256 bytes (rows of 64 and 128 bytes) the swizzle gives each its own 16 bytes.
 template <int RH>
+__device__ __forceinline__ int ex_swz(int r) {
+    if (RH == 32) return (r >> 4) & 3;
+    if (RH == 64) return ((r >> 1) & 1) | (((r >> 4) & 3) << 1);
+    return (r & 3) | (((r >> 4) & 3) << 2);
+}
+
+// FUSED (r_w at most ex_fused_rw(RH)): no Wt comes from memory. The workgroup keeps bf16(Z[s]) in LDS and
+// forms the Wt rows of a chunk itself, wave w those of columns 16 w .. + 15 (V_hat's rows straight into
+// operand registers, loaded a chunk ahead), with the same roundings.
+template <int RH, bool FUSED>
 __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict__ u_hat, const bf16_t* __restrict__ wt,
-                                                       int w, int cpw, bf16_t* __restrict__ x_hat) {
+                                                       const float* __restrict__ z, const bf16_t* __restrict__ v_hat,
+                                                       int h, int w, int rh, int rw, int cpw, bf16_t* __restrict__ x_hat) {
     constexpr int ROWB = RH * 2;         // bytes per Wt row
     constexpr int CHB = kExC * ROWB;     // bytes per chunk
     constexpr int CPR = ROWB / 16;       // 16-byte pieces per row
@@ -680,41 +700,79 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
     constexpr int NLD = CHB / 1024 / 4;  // DMA instructions per wave per chunk
     constexpr int KS = RH / 32;          // k-steps
     __shared__ __attribute__((aligned(1024))) char buf0[CHB];
-    __shared__ __attribute__((aligned(1024))) char buf1[CHB];
+    __shared__ __attribute__((aligned(1024))) char buf1[FUSED ? 1024 : CHB];
     __shared__ __attribute__((aligned(1024))) char ostage[4 * 32 * kExC * 2];
+    constexpr int RW = ex_fused_rw(RH);
+    constexpr int ZP = RW * 2 + 16;  // pitch of the staged Z rows: 16 rows on distinct banks
+    __shared__ __attribute__((aligned(16))) char zs[FUSED ? RH * ZP : 16];
     const int nch = w / kExC;
     const int nranges = (nch + cpw - 1) / cpw;
     const int band = blockIdx.x / nranges;
     const int c0 = (blockIdx.x % nranges) * cpw, c1 = min(c0 + cpw, nch);
+    const bool whole = (band + 1) * kExT <= h;
+    if (!FUSED) wt += (static_cast<int64_t>(blockIdx.y) * w + static_cast<int64_t>(c0) * kExC) * RH;
+    x_hat += static_cast<int64_t>(blockIdx.y) * h * w;
 
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
 
-    // U_hat fragments: token 32 wave + 16 n + l16 of the band, k-run 8 g of step s
+    // Z rounded to bf16 (hardware round-to-nearest-even), zeros past r_h and r_w; V_hat fragments of the
+    // first chunk: row 16 wave + l16, k-run 8 g of step s
+    constexpr int VS = RW / 32;
+    uint4 va[FUSED ? VS : 1];
+    const bf16_t* vrow = v_hat + (static_cast<int64_t>(c0) * kExC + 16 * wave + l16) * rw + 8 * g;
+    auto load_v = [&]() {
+#pragma unroll
+        for (int s = 0; s < (FUSED ? VS : 0); ++s) va[s] = 32 * s + 8 * g < rw ? ldg16(vrow + 32 * s) : make_uint4(0, 0, 0, 0);
+        vrow += static_cast<int64_t>(kExC) * rw;
+    };
+    if constexpr (FUSED) {
+        load_v();
+        constexpr int ZL = RW / 4, ZS = 256 / ZL, ZQ = RH / ZS;  // lanes per row, rows per pass, passes
+        const int zc = tid % ZL, zr = tid / ZL;
+        f32x4 zv[ZQ];
+#pragma unroll
+        for (int q = 0; q < ZQ; ++q)
+            zv[q] = zr + ZS * q < rh && 4 * zc < rw
+                        ? *reinterpret_cast<const f32x4*>(z + (static_cast<int64_t>(blockIdx.y) * rh + zr + ZS * q) * rw + 4 * zc)
+                        : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < ZQ; ++q) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(zv[q][e]);
+            *reinterpret_cast<bf16x4*>(zs + (zr + ZS * q) * ZP + 8 * zc) = o;
+        }
+    }
+
+    // U_hat fragments: token 32 wave + 16 n + l16 of the band (past the last token: the last one, not
+    // stored), k-run 8 g of step s (zero past r_h)
     uint4 fb[2][KS];
-    const bf16_t* urow = u_hat + (static_cast<int64_t>(band) * kExT + 32 * wave + l16) * RH + 8 * g;
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < 2; ++n) {
+        const int t = min(band * kExT + 32 * wave + 16 * n + l16, h - 1);
+        const bf16_t* urow = u_hat + static_cast<int64_t>(t) * rh + 8 * g;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) fb[n][s] = ldg16(urow + 16 * n * RH + 32 * s);
+        for (int s = 0; s < KS; ++s) fb[n][s] = 32 * s + 8 * g < rh ? ldg16(urow + 32 * s) : make_uint4(0, 0, 0, 0);
+    }
 
     // DMA: instruction j of the wave fills bytes 1024 (NLD wave + j) .. + 1023 of a buffer, i.e.
     // row R = RPI (NLD wave + j) + lane / CPR, position lane % CPR
-    const i32x4 rs = enc_rsrc(wt, static_cast<uint32_t>(w) * ROWB);
+    const i32x4 rs = FUSED ? i32x4{0, 0, 0, 0} : enc_rsrc(wt, static_cast<uint32_t>(c1 - c0) * CHB);
     uint32_t voff[NLD];
 #pragma unroll
     for (int j = 0; j < NLD; ++j) {
         const int R = RPI * (NLD * wave + j) + lane / CPR;
-        voff[j] = static_cast<uint32_t>(R * ROWB + (((lane % CPR) ^ ex_swz(R)) * 16));
+        voff[j] = static_cast<uint32_t>(R * ROWB + (((lane % CPR) ^ ex_swz<RH>(R)) * 16));
     }
     auto issue = [&](int c, char* buf) {
         char* base = buf + 1024 * NLD * wave;
 #pragma unroll
         for (int j = 0; j < NLD; ++j)
             raw_buffer_load_lds(rs, reinterpret_cast<lds_void*>(reinterpret_cast<uintptr_t>(base + 1024 * j)), 16,
-                                static_cast<int>(voff[j]), c * CHB, 0, 0);
+                                static_cast<int>(voff[j]), (c - c0) * CHB, 0, 0);
     };
     // A fragments: operand row l16 of block b is chunk row 16 (l16 / 4) + 4 b + l16 % 4
     int rowoff[4], rsw[4];
@@ -722,12 +780,13 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
     for (int b = 0; b < 4; ++b) {
         const int R = 16 * (l16 >> 2) + 4 * b + (l16 & 3);
         rowoff[b] = R * ROWB;
-        rsw[b] = ex_swz(R);
+        rsw[b] = ex_swz<RH>(R);
     }
     // output staging of the wave (32 rows of 128 bytes); store q of a lane: row 8 q + lane / 8 of the
     // wave's tokens, columns 8 (lane % 8) .. + 7 of the chunk
     char* ost = ostage + wave * (32 * kExC * 2);
-    bf16_t* orow = x_hat + (static_cast<int64_t>(band) * kExT + 32 * wave + (lane >> 3)) * w + 8 * (lane & 7);
+    const int trow = band * kExT + 32 * wave + (lane >> 3);
+    bf16_t* orow = x_hat + static_cast<int64_t>(trow) * w + 8 * (lane & 7);
 
     // the previous chunk's results, read back from the staging in store order (named values, not
     // an array: an array read by the deferred stores was kept in scratch memory)
@@ -735,23 +794,64 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
     const int64_t w8 = static_cast<int64_t>(8) * w;
     auto store_pending = [&](int c) {
         bf16_t* dst = orow + c * kExC;
-        *reinterpret_cast<uint4*>(dst) = p0;
-        *reinterpret_cast<uint4*>(dst + w8) = p1;
-        *reinterpret_cast<uint4*>(dst + 2 * w8) = p2;
-        *reinterpret_cast<uint4*>(dst + 3 * w8) = p3;
+        if (whole) {
+            *reinterpret_cast<uint4*>(dst) = p0;
+            *reinterpret_cast<uint4*>(dst + w8) = p1;
+            *reinterpret_cast<uint4*>(dst + 2 * w8) = p2;
+            *reinterpret_cast<uint4*>(dst + 3 * w8) = p3;
+        } else {
+            if (trow < h) *reinterpret_cast<uint4*>(dst) = p0;
+            if (trow + 8 < h) *reinterpret_cast<uint4*>(dst + w8) = p1;
+            if (trow + 16 < h) *reinterpret_cast<uint4*>(dst + 2 * w8) = p2;
+            if (trow + 24 < h) *reinterpret_cast<uint4*>(dst + 3 * w8) = p3;
+        }
     };
-    if (c0 < c1) issue(c0, buf0);
-    for (int c = c0; c < c1; ++c) {
-        const bool odd = (c - c0) & 1;
-        const char* cur = odd ? buf1 : buf0;
-        char* nxt = odd ? buf0 : buf1;
-        // this chunk's rows are in LDS (and the stores issued before its products are done);
-        // after the barrier every wave is done reading the other buffer, which is refilled next
-        __builtin_amdgcn_s_waitcnt(0x0070);
+    // the chunk's Wt rows into buf0: lane holds column 16 wave + l16, rows i = 16 ib + 4 g + e
+    auto form_w = [&]() {
+#pragma unroll
+        for (int ib = 0; ib < RH / 16; ++ib) {
+            f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+            const char* zrow = zs + (16 * ib + l16) * ZP + 16 * g;
+#pragma unroll
+            for (int s = 0; s < VS; ++s)
+                if (32 * s < rw)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(zrow + 64 * s)),
+                        __builtin_bit_cast(bf16x8, va[FUSED ? s : 0]), acc, 0, 0, 0);
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(acc[e]);
+            const int R = 16 * wave + l16;
+            *reinterpret_cast<bf16x4*>(buf0 + R * ROWB + (((2 * ib + (g >> 1)) ^ ex_swz<RH>(R)) * 16) + (g & 1) * 8) = o;
+        }
+    };
+    auto barrier = [&]() {  // with this wave's LDS accesses done
+        __builtin_amdgcn_s_waitcnt(0xC07F);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        if (c + 1 < c1) issue(c + 1, nxt);
+    };
+    if (!FUSED && c0 < c1) issue(c0, buf0);
+    for (int c = c0; c < c1; ++c) {
+        const bool odd = !FUSED && ((c - c0) & 1);
+        const char* cur = odd ? buf1 : buf0;
+        char* nxt = odd ? buf0 : buf1;
+        // this chunk's rows are in LDS; after the barrier every wave is done reading the other
+        // buffer, which is refilled next. The four stores of a whole band that follow the loads stay
+        // in flight (a ragged band may skip some of its stores, so it waits for them all).
+        if constexpr (FUSED) {
+            barrier();  // Z is staged; every wave is done reading the previous chunk's rows
+            form_w();
+            if (c + 1 < c1) load_v();
+            barrier();
+        } else {
+            if (whole && c > c0 + 1) __builtin_amdgcn_s_waitcnt(0x0070 | 4);
+            else __builtin_amdgcn_s_waitcnt(0x0070);
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_barrier" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            if (c + 1 < c1) issue(c + 1, nxt);
+        }
         if (c > c0) store_pending(c - 1);
         f32x4 acc[2][4];
 #pragma unroll
@@ -813,12 +913,11 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
 // on v_mfma_f32_32x32x16_bf16 over K = r_w <= 256, Z as the A operand (lane l: row l % 32,
 // k-run 8 (l / 32) of each 16-wide step) and V_hat as the B operand, so that a lane's results
 // are four runs of four consecutive i of one row j: 8-byte stores.
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 constexpr int kVztT = 64;                // rows j and rows i per workgroup
 constexpr int kVztPitch = 256 * 2 + 16;  // LDS bytes per staged row (r_w <= 256, 16 bytes of skew)
 
 __global__ __launch_bounds__(256) void vzt_kernel(const float* __restrict__ z, const bf16_t* __restrict__ v_hat,
-                                                  int w, int rh, int rw, bf16_t* __restrict__ wt) {
+                                                  int w, int rh, int rw, int ldw, bf16_t* __restrict__ wt) {
     __shared__ __attribute__((aligned(16))) char zs[kVztT * kVztPitch];
     __shared__ __attribute__((aligned(16))) char vs[kVztT * kVztPitch];
     const int j0 = blockIdx.x * kVztT, i0 = blockIdx.y * kVztT, s = blockIdx.z;
@@ -878,14 +977,14 @@ __global__ __launch_bounds__(256) void vzt_kernel(const float* __restrict__ z, c
                                                          acc, 0, 0, 0);
     // lane: row j of Wt, columns i0 + 32 wi + 8 q + 4 lh + e of acc[4 q + e]
     const int j = j0 + 32 * wj + l32;
-    bf16_t* out = wt + (static_cast<int64_t>(s) * w + j) * rh;
+    bf16_t* out = wt + (static_cast<int64_t>(s) * w + j) * ldw;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int i = i0 + 32 * wi + 8 * q + 4 * lh;
-        if (i < rh) {  // r_h is a multiple of 4: the run of four is whole
+        if (i < ldw) {  // r_h is a multiple of 4: the run of four is whole; zeros past it
             bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(acc[4 * q + e]);
+            for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(i < rh ? acc[4 * q + e] : 0.f);
             *reinterpret_cast<bf16x4*>(out + i) = o;
         }
     }
@@ -908,20 +1007,11 @@ __global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float* __restric
 // segment offsets and row maps of the two grouped products (slice s owns rows s*w .. of
 // V_hat Z^T, gathered from row p - s*w of V_hat, and rows s*h .. of X_hat, from row p - s*h
 // of U_hat).
-__global__ __launch_bounds__(256) void codec_prep_kernel(const float* __restrict__ z, int64_t nz,
-                                                         bf16_t* __restrict__ zb, int n, int w, int h,
+__global__ __launch_bounds__(256) void codec_prep_kernel(int n, int w, int h,
                                                          int32_t* __restrict__ seg_w, int32_t* __restrict__ rows_w,
                                                          int32_t* __restrict__ seg_h, int32_t* __restrict__ rows_h) {
     const int64_t tid = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
-    if (zb)
-        for (int64_t i = tid * 4; i < nz; i += stride * 4) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(z + i);
-            uint2 o;
-            o.x = static_cast<uint32_t>(f32_to_bf16(v[0])) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
-            o.y = static_cast<uint32_t>(f32_to_bf16(v[2])) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
-            *reinterpret_cast<uint2*>(zb + i) = o;
-        }
     for (int64_t i = tid; i < static_cast<int64_t>(n) * w; i += stride) rows_w[i] = static_cast<int32_t>(i % w);
     for (int64_t i = tid; i < static_cast<int64_t>(n) * h; i += stride) rows_h[i] = static_cast<int32_t>(i % h);
     for (int64_t i = tid; i <= n; i += stride) {
@@ -1076,43 +1166,52 @@ hipError_t launch_decode_small(DType dt, const float* z, const void* u_hat, cons
     return hipGetLastError();
 }
 
-hipError_t launch_codec_prep(const float* z, int64_t nz, void* zb, int n, int w, int h, int32_t* seg_w,
-                             int32_t* rows_w, int32_t* seg_h, int32_t* rows_h, hipStream_t s) {
-    const int64_t work = std::max<int64_t>({nz / 4, static_cast<int64_t>(n) * std::max(w, h), n + 1});
+hipError_t launch_codec_prep(int n, int w, int h, int32_t* seg_w, int32_t* rows_w, int32_t* seg_h, int32_t* rows_h,
+                             hipStream_t s) {
+    const int64_t work = std::max<int64_t>(static_cast<int64_t>(n) * std::max(w, h), n + 1);
     const int grid = static_cast<int>(std::min<int64_t>((work + 255) / 256, 4096));
     ProfileScope prof("codec_prep", s);
-    hipLaunchKernelGGL(codec_prep_kernel, dim3(grid), dim3(256), 0, s, z, nz, static_cast<bf16_t*>(zb), n, w, h,
-                       seg_w, rows_w, seg_h, rows_h);
+    hipLaunchKernelGGL(codec_prep_kernel, dim3(grid), dim3(256), 0, s, n, w, h, seg_w, rows_w, seg_h, rows_h);
     return hipGetLastError();
 }
 
-bool vzt_ok(DType dt, int w, int rh, int rw) {
-    return dt == DType::BF16 && w % kVztT == 0 && rh > 0 && rh % 4 == 0 && rw > 0 && rw % 16 == 0 && rw <= 256;
-}
+int expand_rank(int rh) { return rh <= 32 ? 32 : rh <= 64 ? 64 : rh <= 128 ? 128 : 256; }
 
-hipError_t launch_vzt(const float* z, const void* v_hat, int w, int rh, int rw, int slices, void* wt, hipStream_t s) {
-    ProfileScope prof("codec_vzt", s);
-    hipLaunchKernelGGL(vzt_kernel, dim3(w / kVztT, (rh + kVztT - 1) / kVztT, slices), dim3(256), 0, s, z,
-                       static_cast<const bf16_t*>(v_hat), w, rh, rw, static_cast<bf16_t*>(wt));
-    return hipGetLastError();
-}
-
-bool expand_ok(DType dt, int h, int w, int rh) {
-    return dt == DType::BF16 && h > 0 && h % kExT == 0 && w > 0 && w % kExC == 0 && (rh == 128 || rh == 256);
-}
-
-hipError_t launch_expand(const void* u_hat, const void* wt, int h, int w, int rh, void* x_hat, hipStream_t s) {
+hipError_t launch_decode_bf16(const float* z, const void* u_hat, const void* v_hat, int h, int w, int rh, int rw,
+                              int slices, void* wt, void* x_hat, hipStream_t s) {
+    const int rp = expand_rank(rh);
+    // One launch where forming Wt in every band costs less than the launch it saves: padded ranks up
+    // to 64 always (4 x 256 x 768 ranks 64: 12.9 -> 7.5 us; 4096 x 4096 ranks 64: 13.9 -> 13.3), rank
+    // 128 up to one round of the machine (4001 x 512 ranks 128 x 32: 10.0 -> 7.6 us; 1024 tiles the
+    // same; 4096 x 4096 ranks 128, 2048 tiles: 15.9 against 20.1 us fused).
+    const int64_t bands = (h + kExT - 1) / kExT, nch = w / kExC;
+    const bool fused = rw <= ex_fused_rw(rp) && (rp <= 64 || bands * nch * slices <= 512);
+    if (!fused) {
+        ProfileScope prof("codec_vzt", s);
+        hipLaunchKernelGGL(vzt_kernel, dim3(w / kVztT, (rp + kVztT - 1) / kVztT, slices), dim3(256), 0, s, z,
+                           static_cast<const bf16_t*>(v_hat), w, rh, rw, rp, static_cast<bf16_t*>(wt));
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     // about two workgroups per CU: the chunk runs are as short as that allows
-    const int64_t bands = h / kExT, nch = w / kExC;
-    const int cpw = static_cast<int>(std::max<int64_t>(1, (bands * nch + 511) / 512));
-    const int64_t grid = bands * ((nch + cpw - 1) / cpw);
-    ProfileScope prof("codec_uw", s);
-    if (rh == 256)
-        hipLaunchKernelGGL(expand_kernel<256>, dim3(static_cast<unsigned>(grid)), dim3(256), 0, s,
-                           static_cast<const bf16_t*>(u_hat), static_cast<const bf16_t*>(wt), w, cpw, static_cast<bf16_t*>(x_hat));
-    else
-        hipLaunchKernelGGL(expand_kernel<128>, dim3(static_cast<unsigned>(grid)), dim3(256), 0, s,
-                           static_cast<const bf16_t*>(u_hat), static_cast<const bf16_t*>(wt), w, cpw, static_cast<bf16_t*>(x_hat));
+    const int cpw = static_cast<int>(std::max<int64_t>(1, (bands * nch * slices + 511) / 512));
+    const dim3 grid(static_cast<unsigned>(bands * ((nch + cpw - 1) / cpw)), slices);
+    ProfileScope prof(fused ? "codec_decode" : "codec_uw", s);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, static_cast<const bf16_t*>(u_hat),
+                           static_cast<const bf16_t*>(wt), z, static_cast<const bf16_t*>(v_hat), h, w, rh, rw, cpw,
+                           static_cast<bf16_t*>(x_hat));
+    };
+    if (fused) {
+        if (rp == 32) go(&expand_kernel<32, true>);
+        else if (rp == 64) go(&expand_kernel<64, true>);
+        else go(&expand_kernel<128, true>);
+    } else {
+        if (rp == 32) go(&expand_kernel<32, false>);
+        else if (rp == 64) go(&expand_kernel<64, false>);
+        else if (rp == 128) go(&expand_kernel<128, false>);
+        else go(&expand_kernel<256, false>);
+    }
     return hipGetLastError();
 }
 

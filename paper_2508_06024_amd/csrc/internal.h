@@ -101,10 +101,16 @@ hipError_t launch_encode_small(DType dt, const void* x, const void* u, const voi
 hipError_t launch_decode_small(DType dt, const float* z, const void* u_hat, const void* v_hat, int h, int w, int rh,
                                int rw, int slices, void* x_hat, hipStream_t s);
 hipError_t launch_encode_fused(const EncArgs& a, float* z, hipStream_t s);
-// Decoder set-up of n slices: zb = bfloat16(z) (nz elements, a multiple of 4; skipped when zb is
-// null); seg_w[s] = s*w, rows_w[p] = p % w, seg_h[s] = s*h, rows_h[p] = p % h (s <= n).
-hipError_t launch_codec_prep(const float* z, int64_t nz, void* zb, int n, int w, int h, int32_t* seg_w,
-                             int32_t* rows_w, int32_t* seg_h, int32_t* rows_h, hipStream_t s);
+// Set-up of the float32 decoder for n slices: seg_w[s] = s*w, rows_w[p] = p % w, seg_h[s] = s*h,
+// rows_h[p] = p % h (s <= n).
+hipError_t launch_codec_prep(int n, int w, int h, int32_t* seg_w, int32_t* rows_w, int32_t* seg_h, int32_t* rows_h,
+                             hipStream_t s);
+// Decoder of bf16 layers in two launches: Wt[s] = V_hat bf16(Z[s])^T, rounded to bf16, into wt
+// [slices][w][expand_rank(r_h)] (zeros past r_h), then X_hat[s] = U_hat Wt[s]^T (w a multiple of 128;
+// r_h, r_w multiples of 16, at most 256).
+int expand_rank(int rh);
+hipError_t launch_decode_bf16(const float* z, const void* u_hat, const void* v_hat, int h, int w, int rh, int rw,
+                              int slices, void* wt, void* x_hat, hipStream_t s);
 // ---------------------------------------------------------------- codec fitting
 // The fit runs its two sides (U and V) in lockstep: each launch below takes both.
 // g = y^T y in float64 (y [n][r] float32, g [r][r], the 64 x 64 tiles on and above the diagonal)
@@ -148,14 +154,6 @@ hipError_t launch_unfold(DType dt, const void* x, int c, int h, int w, void* xu,
 
 // dst = bfloat16(src) with round-to-nearest-even, n a multiple of 4
 hipError_t launch_f32_to_bf16(const float* src, int64_t n, void* dst, hipStream_t s);
-// Decoder product Wt[s] = V_hat bf16(Z[s])^T [w][r_h] in one launch for bf16 layers
-// (w a multiple of 64, r_h of 4, r_w of 16 and at most 256); vzt_ok tells whether the shape qualifies.
-bool vzt_ok(DType dt, int w, int rh, int rw);
-hipError_t launch_vzt(const float* z, const void* v_hat, int w, int rh, int rw, int slices, void* wt, hipStream_t s);
-// Decoder product X_hat = U_hat Wt^T [h][w] (bf16, one slice) in one launch: U_hat [h][r_h], Wt [w][r_h],
-// h a multiple of 128, w of 64, r_h 128 or 256; expand_ok tells whether the shape qualifies.
-bool expand_ok(DType dt, int h, int w, int rh);
-hipError_t launch_expand(const void* u_hat, const void* wt, int h, int w, int rh, void* x_hat, hipStream_t s);
 
 
 }  // namespace ec2moe

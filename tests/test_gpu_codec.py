@@ -51,14 +51,17 @@ def test_full_rank_codec_round_trips_on_gpu():
     (3, 128, 256, 80, 128, W.BF16),   # r_h inside the second 64-row block, two column tiles
     (2, 256, 384, 256, 192, W.BF16),  # three column tiles of a token tile placed on one XCD
     (17, 128, 128, 16, 64, W.BF16),   # two tiles per slice, more slices than one batch
-    # one slice of whole 128-token bands with r_h = 128 or 256 takes the decoder's expansion kernel:
+    # the decoder's expansion kernel in whole 128-token bands:
     (1, 128, 128, 128, 64, W.BF16),    # one band of two 64-column chunks
     (1, 256, 512, 256, 128, W.BF16),   # with the fused encoder
+    (1, 4000, 2176, 48, 32, W.BF16),   # runs of three chunks, a ragged last band, rank padded to 64
+    (3, 129, 256, 64, 256, W.BF16),    # one launch, the largest r_w, one token in the second band
+    (1, 200, 384, 112, 112, W.BF16),   # one launch with padded ranks of 128
     (1, 4096, 2176, 128, 64, W.BF16),  # runs of three chunks, the last of each band one chunk (34 chunks)
     # ... with a last tile of one token or column block, and the width in shares of unequal stages:
     (1, 65, 1152, 64, 16, W.BF16),     # 9 stages in 4 shares, one token in the second tile
     (1, 127, 128, 16, 80, W.BF16),     # one stage
-    (2, 1000, 640, 144, 208, W.BF16),  # tiles that fill the machine: one share
+    (2, 1000, 640, 144, 208, W.BF16),  # tiles of two slices in one share
     # at most 64 tokens per slice take the small-batch encoder and decoder:
     (3, 48, 256, 32, 48, W.BF16),
     (2, 64, 256, 64, 256, W.F32),     # the largest r_h and r_w of that path

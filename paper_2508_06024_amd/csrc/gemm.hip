@@ -18,7 +18,7 @@
 // double buffered. Weight rows feed the MFMA A operand and token rows the B operand, so every
 // lane ends with 4 consecutive output columns of one token row (one 8- or 16-byte store).
 //
-// Three mainloops:
+// Four mainloops:
 //   * gemm_pp_kernel (bf16 256x256 tiles, K a multiple of 128, 32x32x16 MFMA): persistent
 //     (one workgroup per CU, each XCD's workgroups stepping through consecutive tiles
 //     together); buffer loads write the slabs straight into LDS (no register staging; two
@@ -29,6 +29,8 @@
 //     summed in order by a second kernel);
 //   * gemm_lds_kernel (bf16 128x128 tiles, same loads and split): 4 waves that each
 //     interleave their own loads, fragment reads and MFMAs;
+//   * gemm_stream_kernel (grouped bf16 products with few rows per group): a ring of LDS slabs
+//     filled by the same loads, for the weight stream of small batches;
 //   * gemm_kernel (any K that is a multiple of the 16-byte chunk, bf16 or fp32): loads
 //     through registers, zero-filling chunks past K; one workgroup per tile, the
 //     workgroup-to-tile map rotated over the XCDs.
@@ -415,6 +417,142 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
     r[2] = uniform(static_cast<int>(bytes));
     r[3] = 0x00020000;  // raw (untyped, unswizzled) buffer of the gfx9 family
     return r;
+}
+
+// ------------------------------------------------------------------ streaming mainloop
+//
+// Grouped bf16 products with few rows per group (a decoding step, small experts): every weight row is
+// read once for a handful of token rows, so the kernel is a stream of the active groups' weights and
+// its speed is the bytes it keeps in flight (32 experts of 8 rows, 4096 -> 1536 -> 4096: 1.5 GB of
+// weights in a call of 238 us, 6.3 TB/s; 278 us with the register-staged tile, which holds one slab
+// in flight and stores it to LDS between two barriers). A workgroup computes TM x 128 tiles over the whole K;
+// its slabs (128-byte pieces of each row) go through a ring of RING LDS stages filled by
+// buffer_load ... lds, RING - 1 of them in flight behind counted waits and one barrier per slab, and
+// two workgroups share a CU (80 KB each), so that one's start overlaps the other's stream. Four waves
+// of TM x 32 on v_mfma_f32_16x16x32_bf16; each ring slot is its own LDS object, named at compile time
+// where it is read, so that a fragment read waits for no later load.
+template <typename TO, int TM, int TN, bool SWIGLU, int RING, bool NT>
+__global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
+    constexpr int CPR = 8;                  // 16-byte chunks per slab row
+    constexpr int BK = CPR * 8;             // elements of K per slab
+    constexpr int ROWB = CPR * 16;          // bytes per staged row
+    constexpr int RPI = 1024 / ROWB;        // rows per load instruction (1 KB)
+    constexpr int NLD = (TM + TN) / RPI / 4;  // load instructions per wave per slab
+    constexpr int MI = TM / 16, NI = TN / 64;
+    constexpr int NOUT = SWIGLU ? TN / 2 : TN;
+    constexpr int STAGE = (TM + TN) * ROWB;
+    static_assert((TM + TN) % (4 * RPI) == 0 && TM % RPI == 0, "whole load instructions");
+    static_assert(!SWIGLU || NI % 2 == 0, "SwiGLU waves hold matching gate/up blocks");
+    static_assert((RING == 3 || RING == 4) && (RING - 2) * NLD <= 63, "counted waits");
+    __shared__ __attribute__((aligned(1024))) char lds0[STAGE];
+    __shared__ __attribute__((aligned(1024))) char lds1[STAGE];
+    __shared__ __attribute__((aligned(1024))) char lds2[STAGE];
+    __shared__ __attribute__((aligned(1024))) char lds3[RING > 3 ? STAGE : 16];
+
+    const int ntn = (a.N + NOUT - 1) / NOUT;
+    TileInfo ti;
+    if (!find_tile<TM>(a, ntn, ti)) return;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = uniform(tid >> 6);
+    const int l16 = lane & 15, lg = lane >> 4;
+    const uint32_t row_bytes = static_cast<uint32_t>(a.K) * 2u;
+
+    // load instruction j of the wave fills staged rows RPI (NLD wave + j) .. (token rows first, then
+    // weight rows); chunk c of row R sits at c ^ swz(R), applied on the global side. Token rows past
+    // the tile's repeat its last one (not stored).
+    auto swz = [](int R) { return (R >> 1) & 7; };
+    const i32x4 rtok = buffer_rsrc(a.tok, static_cast<uint32_t>(a.src_rows * row_bytes));
+    const i32x4 rw = buffer_rsrc(static_cast<const bf16_t*>(a.w) + static_cast<int64_t>(ti.group) * a.w_group_stride,
+                                 static_cast<uint32_t>(a.w_rows * row_bytes));
+    uint32_t voff[NLD];
+#pragma unroll
+    for (int j = 0; j < NLD; ++j) {
+        const int R = RPI * (NLD * wave + j) + lane / CPR;
+        int64_t src;
+        if (R < TM) {
+            const int64_t pos = ti.row0 + std::min(R, ti.valid - 1);
+            src = a.row_index ? a.row_index[pos] : pos;
+        } else {
+            src = weight_row<TN, SWIGLU>(a, ti.nt, R - TM);
+        }
+        voff[j] = static_cast<uint32_t>(src) * row_bytes + static_cast<uint32_t>(((lane % CPR) ^ swz(R)) * 16);
+    }
+    auto issue = [&](int st, char* slot) {
+        char* base = slot + 1024 * NLD * wave;
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) {
+            const bool tok = RPI * (NLD * wave + j) < TM;  // uniform
+            lds_void* dst = reinterpret_cast<lds_void*>(reinterpret_cast<uintptr_t>(base + 1024 * j));
+            if (tok) raw_buffer_load_lds(rtok, dst, 16, static_cast<int>(voff[j]), st * ROWB, 0, 0);
+            else raw_buffer_load_lds(rw, dst, 16, static_cast<int>(voff[j]), st * ROWB, 0, NT ? 2 : 0);
+        }
+    };
+
+    int foff_t[MI], foff_w[NI], sw_t[MI], sw_w[NI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+        const int R = mi * 16 + l16;
+        foff_t[mi] = R * ROWB;
+        sw_t[mi] = swz(R);
+    }
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        const int R = TM + weight_frag_row<TN, 4, NI, SWIGLU>(wave, ni, l16);
+        foff_w[ni] = R * ROWB;
+        sw_w[ni] = swz(R);
+    }
+    f32x4 acc[NI][MI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int ns = a.K / BK;
+    auto step = [&](int st, const char* cur, char* refill) {
+        if (st >= ns) return;
+        // slabs issued after this one stay in flight
+        const int later = std::min(RING - 2, ns - 1 - st);
+        if (RING == 4 && later >= 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NLD));
+        else if (later >= 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NLD));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        // every wave's loads of this slab have landed, and every wave is done with the previous
+        // slab, whose slot is refilled next
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if (st + RING - 1 < ns) issue(st + RING - 1, refill);
+#pragma unroll
+        for (int q = 0; q < CPR / 4; ++q) {
+            uint4 bt[MI], aw[NI];
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+                bt[mi] = *reinterpret_cast<const uint4*>(cur + foff_t[mi] + (((4 * q + lg) ^ sw_t[mi]) * 16));
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+                aw[ni] = *reinterpret_cast<const uint4*>(cur + foff_w[ni] + (((4 * q + lg) ^ sw_w[ni]) * 16));
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = Mfma<bf16_t>::step(aw[ni], bt[mi], acc[ni][mi]);
+        }
+    };
+    issue(0, lds0);
+    if (ns > 1) issue(1, lds1);
+    if (RING == 4 && ns > 2) issue(2, lds2);
+    for (int st = 0; st < ns; st += RING) {
+        if constexpr (RING == 3) {
+            step(st, lds0, lds2);
+            step(st + 1, lds1, lds0);
+            step(st + 2, lds2, lds1);
+        } else {
+            step(st, lds0, lds3);
+            step(st + 1, lds1, lds0);
+            step(st + 2, lds2, lds1);
+            step(st + 3, lds3, lds2);
+        }
+    }
+    write_tile<TO, TM, TN, 1, 4, MI, NI, SWIGLU>(a, ti, 0, wave, lane, acc);
 }
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -1144,6 +1282,16 @@ hipError_t run(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <typename TO, int TM, int TN, bool SWIGLU, int RING, bool NT>
+hipError_t run_stream(const GemmArgs& a, hipStream_t s) {
+    const int64_t grid = grid_size<TM, TN, SWIGLU>(a);
+    if (grid == 0) return hipSuccess;
+    ProfileScope prof(a.name ? a.name : "gemm", s);
+    hipLaunchKernelGGL((gemm_stream_kernel<TO, TM, TN, SWIGLU, RING, NT>), dim3(static_cast<unsigned>(grid)), dim3(256),
+                       0, s, a);
+    return hipGetLastError();
+}
+
 template <int TM, int TN, int WM, int WN, bool SWIGLU, typename TO>
 hipError_t run_lds(const GemmArgs& a, hipStream_t s) {
     if (grid_size<TM, TN, SWIGLU>(a) == 0) return hipSuccess;
@@ -1216,6 +1364,36 @@ Tile choose_tile(const GemmArgs& a, bool swiglu, bool lds) {
     return Tile::Small;
 }
 
+// Tile of the streaming kernel (times of whole expert calls, inputs changed from pass to pass, against
+// the register-staged 32 x 128 tile):
+//   * 32 token rows below 16 rows a group (counted over all groups, active or not), else 64, so
+//     that most groups read their weights once: 32 experts of 8 rows, 4096 -> 1536 -> 4096, 278 ->
+//     239 us with 32 rows; 25 active of 64 experts, 768 -> 3072 -> 768, 1024 tokens, 90 -> 76 with 64;
+//   * 64 weight rows where 128 leave the launch under one round of two workgroups a CU: 8 experts of
+//     1-2 rows, 4096 x 8192: 247 -> 228 us with 128 rows, 219 with 64;
+//   * the weights pass the caches by (streaming policy) while a group has one token tile or so:
+//     278 -> 237 against 268 us without; 8 groups of 128 rows: 46 us with it, 42 without.
+template <typename TO, bool SWIGLU>
+hipError_t run_stream_for(const GemmArgs& a, hipStream_t s) {
+    const int64_t rows_per_group = a.rows / std::max(1, a.n_groups);
+    const int tm = rows_per_group < 16 ? 32 : 64;
+    const int64_t tiles = (std::min<int64_t>(a.rows, a.n_groups) + a.rows / tm) * (a.N / 128);
+    const bool narrow = !SWIGLU && tiles < 2 * kCUs;
+    if (tm == 32) {
+        if constexpr (!SWIGLU)
+            if (narrow) return run_stream<TO, 32, 64, SWIGLU, 4, true>(a, s);
+        return run_stream<TO, 32, 128, SWIGLU, 4, true>(a, s);
+    }
+    if (rows_per_group < 64) {
+        if constexpr (!SWIGLU)
+            if (narrow) return run_stream<TO, 64, 64, SWIGLU, 4, true>(a, s);
+        return run_stream<TO, 64, 128, SWIGLU, 3, true>(a, s);
+    }
+    if constexpr (!SWIGLU)
+        if (narrow) return run_stream<TO, 64, 64, SWIGLU, 4, false>(a, s);
+    return run_stream<TO, 64, 128, SWIGLU, 3, false>(a, s);
+}
+
 template <typename T, typename TO, bool SWIGLU>
 hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
     constexpr bool kLdsPath = sizeof(T) == 2;
@@ -1229,12 +1407,14 @@ hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
             if constexpr (kLdsPath)
                 if (lds_ok) return run_lds<128, 128, 2, 2, SWIGLU, TO>(a, s);
             return run<T, TO, 128, 128, 2, 2, SWIGLU>(a, s);
-        // the small tile streams its whole K a slab at a time: wider slab rows (fewer slabs) for
-        // long K, e.g. the 64-expert ReLU layer's output layer (K = 3072): 38.2 against 48.9 us
-        // with 256-byte rows, the decode workload's gate-up (K = 4096): 181 against 187 us with
-        // 512-byte rows; short K keeps 128-byte rows (K = 768: 19.9 against 22.9 us)
+        // float32 and dense products: the small tile takes its whole K a slab at a time, with wider
+        // slab rows (fewer slabs) for long K, and for any K where the launch has at most one workgroup
+        // per CU: each slab is then a round trip that nothing overlaps (float32 layer of 64 tokens,
+        // K = 128 and 256, 44.6 us a step with 128-byte rows, 44.1 with 512-byte rows)
         default:
-            if (a.K >= 4096) return run<T, TO, 32, 128, 1, 4, SWIGLU, 32>(a, s);
+            if constexpr (kLdsPath)
+                if (lds_ok && a.seg) return run_stream_for<TO, SWIGLU>(a, s);
+            if (a.K >= 4096 || grid_size<32, 128, SWIGLU>(a) <= kCUs) return run<T, TO, 32, 128, 1, 4, SWIGLU, 32>(a, s);
             if (a.K >= 2048) return run<T, TO, 32, 128, 1, 4, SWIGLU, 16>(a, s);
             return run<T, TO, 32, 128, 1, 4, SWIGLU, 8>(a, s);
     }

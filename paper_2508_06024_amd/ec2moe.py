@@ -112,6 +112,9 @@ for _name, _args in _SIGS.items():
 EXPORTS = tuple(_SIGS)
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _check(status: int):
     if status != 0:
         raise Ec2moeError(status, _lib.ec2moe_last_error().decode())
@@ -122,7 +125,11 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device. torch.cuda.current_stream() builds a Stream object
+    in Python, 3 us of a call whose launches cost about 4 us each; the raw handle is the same stream."""
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(torch._C._cuda_getDevice()))
 
 
 def dtype_code(dt: torch.dtype) -> int:

@@ -29,8 +29,8 @@
 //     summed in order by a second kernel);
 //   * gemm_lds_kernel (bf16 128x128 tiles, same loads and split): 4 waves that each
 //     interleave their own loads, fragment reads and MFMAs;
-//   * gemm_stream_kernel (grouped bf16 products with few rows per group): a ring of LDS slabs
-//     filled by the same loads, for the weight stream of small batches;
+//   * gemm_stream_kernel (grouped bf16 products with few rows per group; float32 products): a ring
+//     of LDS slabs filled by the same loads, for the weight stream of small batches;
 //   * gemm_kernel (any K that is a multiple of the 16-byte chunk, bf16 or fp32): loads
 //     through registers, zero-filling chunks past K; one workgroup per tile, the
 //     workgroup-to-tile map rotated over the XCDs.
@@ -421,7 +421,7 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
 
 // ------------------------------------------------------------------ streaming mainloop
 //
-// Grouped bf16 products with few rows per group (a decoding step, small experts): every weight row is
+// Grouped products with few rows per group (a decoding step, small experts): every weight row is
 // read once for a handful of token rows, so the kernel is a stream of the active groups' weights and
 // its speed is the bytes it keeps in flight (32 experts of 8 rows, 4096 -> 1536 -> 4096: 1.5 GB of
 // weights in a call of 238 us, 6.3 TB/s; 278 us with the register-staged tile, which holds one slab
@@ -431,10 +431,10 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
 // two workgroups share a CU (80 KB each), so that one's start overlaps the other's stream. Four waves
 // of TM x 32 on v_mfma_f32_16x16x32_bf16; each ring slot is its own LDS object, named at compile time
 // where it is read, so that a fragment read waits for no later load.
-template <typename TO, int TM, int TN, bool SWIGLU, int RING, bool NT>
+template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, bool NT>
 __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
     constexpr int CPR = 8;                  // 16-byte chunks per slab row
-    constexpr int BK = CPR * 8;             // elements of K per slab
+    constexpr int BK = CPR * Elem<T>::kPerChunk;  // elements of K per slab
     constexpr int ROWB = CPR * 16;          // bytes per staged row
     constexpr int RPI = 1024 / ROWB;        // rows per load instruction (1 KB)
     constexpr int NLD = (TM + TN) / RPI / 4;  // load instructions per wave per slab
@@ -456,14 +456,14 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = uniform(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
-    const uint32_t row_bytes = static_cast<uint32_t>(a.K) * 2u;
+    const uint32_t row_bytes = static_cast<uint32_t>(a.K * sizeof(T));
 
     // load instruction j of the wave fills staged rows RPI (NLD wave + j) .. (token rows first, then
     // weight rows); chunk c of row R sits at c ^ swz(R), applied on the global side. Token rows past
     // the tile's repeat its last one (not stored).
     auto swz = [](int R) { return (R >> 1) & 7; };
     const i32x4 rtok = buffer_rsrc(a.tok, static_cast<uint32_t>(a.src_rows * row_bytes));
-    const i32x4 rw = buffer_rsrc(static_cast<const bf16_t*>(a.w) + static_cast<int64_t>(ti.group) * a.w_group_stride,
+    const i32x4 rw = buffer_rsrc(static_cast<const T*>(a.w) + static_cast<int64_t>(ti.group) * a.w_group_stride,
                                  static_cast<uint32_t>(a.w_rows * row_bytes));
     uint32_t voff[NLD];
 #pragma unroll
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-                for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = Mfma<bf16_t>::step(aw[ni], bt[mi], acc[ni][mi]);
+                for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = Mfma<T>::step(aw[ni], bt[mi], acc[ni][mi]);
         }
     };
     issue(0, lds0);
@@ -1282,12 +1282,12 @@ hipError_t run(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename TO, int TM, int TN, bool SWIGLU, int RING, bool NT>
+template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, bool NT>
 hipError_t run_stream(const GemmArgs& a, hipStream_t s) {
     const int64_t grid = grid_size<TM, TN, SWIGLU>(a);
     if (grid == 0) return hipSuccess;
     ProfileScope prof(a.name ? a.name : "gemm", s);
-    hipLaunchKernelGGL((gemm_stream_kernel<TO, TM, TN, SWIGLU, RING, NT>), dim3(static_cast<unsigned>(grid)), dim3(256),
+    hipLaunchKernelGGL((gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING, NT>), dim3(static_cast<unsigned>(grid)), dim3(256),
                        0, s, a);
     return hipGetLastError();
 }
@@ -1364,6 +1364,13 @@ Tile choose_tile(const GemmArgs& a, bool swiglu, bool lds) {
     return Tile::Small;
 }
 
+// Whole slabs, and operands within 32-bit byte offsets
+template <typename T>
+bool stream_ok(const GemmArgs& a) {
+    const int64_t row_bytes = static_cast<int64_t>(a.K) * sizeof(T);
+    return row_bytes % 128 == 0 && a.src_rows * row_bytes < (int64_t(1) << 32) && a.w_rows * row_bytes < (int64_t(1) << 32);
+}
+
 // Tile of the streaming kernel (times of whole expert calls, inputs changed from pass to pass, against
 // the register-staged 32 x 128 tile):
 //   * 32 token rows below 16 rows a group (counted over all groups, active or not), else 64, so
@@ -1373,31 +1380,36 @@ Tile choose_tile(const GemmArgs& a, bool swiglu, bool lds) {
 //     1-2 rows, 4096 x 8192: 247 -> 228 us with 128 rows, 219 with 64;
 //   * the weights pass the caches by (streaming policy) while a group has one token tile or so:
 //     278 -> 237 against 268 us without; 8 groups of 128 rows: 46 us with it, 42 without.
-template <typename TO, bool SWIGLU>
+template <typename T, typename TO, bool SWIGLU>
 hipError_t run_stream_for(const GemmArgs& a, hipStream_t s) {
     const int64_t rows_per_group = a.rows / std::max(1, a.n_groups);
     const int tm = rows_per_group < 16 ? 32 : 64;
     const int64_t tiles = (std::min<int64_t>(a.rows, a.n_groups) + a.rows / tm) * (a.N / 128);
     const bool narrow = !SWIGLU && tiles < 2 * kCUs;
+    // dense (float32): the small tile, three workgroups a CU, so that each SIMD has products to issue
+    // while another wave waits at its barrier
+    if constexpr (!SWIGLU)
+        if (!a.seg) return run_stream<T, TO, 32, 64, SWIGLU, 4, false>(a, s);
     if (tm == 32) {
         if constexpr (!SWIGLU)
-            if (narrow) return run_stream<TO, 32, 64, SWIGLU, 4, true>(a, s);
-        return run_stream<TO, 32, 128, SWIGLU, 4, true>(a, s);
+            if (narrow) return run_stream<T, TO, 32, 64, SWIGLU, 4, true>(a, s);
+        return run_stream<T, TO, 32, 128, SWIGLU, 4, true>(a, s);
     }
     if (rows_per_group < 64) {
         if constexpr (!SWIGLU)
-            if (narrow) return run_stream<TO, 64, 64, SWIGLU, 4, true>(a, s);
-        return run_stream<TO, 64, 128, SWIGLU, 3, true>(a, s);
+            if (narrow) return run_stream<T, TO, 64, 64, SWIGLU, 4, true>(a, s);
+        return run_stream<T, TO, 64, 128, SWIGLU, 3, true>(a, s);
     }
     if constexpr (!SWIGLU)
-        if (narrow) return run_stream<TO, 64, 64, SWIGLU, 4, false>(a, s);
-    return run_stream<TO, 64, 128, SWIGLU, 3, false>(a, s);
+        if (narrow) return run_stream<T, TO, 64, 64, SWIGLU, 4, false>(a, s);
+    return run_stream<T, TO, 64, 128, SWIGLU, 3, false>(a, s);
 }
 
 template <typename T, typename TO, bool SWIGLU>
 hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
     constexpr bool kLdsPath = sizeof(T) == 2;
     const bool lds_ok = kLdsPath && a.K % 128 == 0;
+    const bool one_slab = a.seg && a.K <= 256 && grid_size<32, 128, SWIGLU>(a) <= kCUs;  // float32
     switch (choose_tile(a, SWIGLU, lds_ok)) {
         case Tile::Big:
             if constexpr (kLdsPath)
@@ -1407,13 +1419,14 @@ hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
             if constexpr (kLdsPath)
                 if (lds_ok) return run_lds<128, 128, 2, 2, SWIGLU, TO>(a, s);
             return run<T, TO, 128, 128, 2, 2, SWIGLU>(a, s);
-        // float32 and dense products: the small tile takes its whole K a slab at a time, with wider
-        // slab rows (fewer slabs) for long K, and for any K where the launch has at most one workgroup
-        // per CU: each slab is then a round trip that nothing overlaps (float32 layer of 64 tokens,
-        // K = 128 and 256, 44.6 us a step with 128-byte rows, 44.1 with 512-byte rows)
+        // The streaming kernel for grouped bf16 and all float32 products (4096 x 4096 x 256 in float32:
+        // 100 -> 82 us; 12 experts, 1024 x 512, 64 tokens: 52 -> 44 us), except grouped float32 ones
+        // with at most a workgroup per CU and K in one or two 512-byte slabs of the register-staged
+        // tile, a round trip each (layer of 64 tokens, K = 128 and 256: 44.1 us a step, 45.0 with the
+        // ring). What is left (dense bf16, K no whole number of 128-byte pieces, operands past 4 GiB)
+        // takes that tile, with wider slab rows for long K.
         default:
-            if constexpr (kLdsPath)
-                if (lds_ok && a.seg) return run_stream_for<TO, SWIGLU>(a, s);
+            if ((kLdsPath ? a.seg != nullptr : !one_slab) && stream_ok<T>(a)) return run_stream_for<T, TO, SWIGLU>(a, s);
             if (a.K >= 4096 || grid_size<32, 128, SWIGLU>(a) <= kCUs) return run<T, TO, 32, 128, 1, 4, SWIGLU, 32>(a, s);
             if (a.K >= 2048) return run<T, TO, 32, 128, 1, 4, SWIGLU, 16>(a, s);
             return run<T, TO, 32, 128, 1, 4, SWIGLU, 8>(a, s);

@@ -34,9 +34,7 @@ constexpr int kMaxExperts = 256;
 constexpr int kChunk = 8;           // logits of one group read together in phase 3
 constexpr int kSplitWaves = 4;      // waves of the split-d workgroups (small batches)
 constexpr int kSplitMaxTiles = 64;  // 16-token tiles below which d is split (given a workspace)
-// d-splits per tile at most: the routing launch, one workgroup per tile, waits for a load per split
-// (32 tokens of 4096, 72 rows: 12.6 us with 32, 12.1 with 16, 13.0 with 8)
-constexpr int kMaxSplit = 16;
+constexpr int kMaxSplit = 32;       // d-splits per tile at most
 constexpr int kSplitMinD = 2048;    // narrower gates run unsplit (the second launch costs more)
 constexpr int kRouteWaves = 8;      // waves of the routing workgroups after a split (16 up to 96 rows)
 

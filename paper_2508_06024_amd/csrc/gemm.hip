@@ -1420,7 +1420,7 @@ hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
                 if (lds_ok) return run_lds<128, 128, 2, 2, SWIGLU, TO>(a, s);
             return run<T, TO, 128, 128, 2, 2, SWIGLU>(a, s);
         // The streaming kernel for grouped bf16 and all float32 products (4096 x 4096 x 256 in float32:
-        // 100 -> 82 us; 12 experts, 1024 x 512, 64 tokens: 52 -> 44 us), except grouped float32 ones
+        // 100 -> about 80 us; 12 experts, 1024 x 512, 64 tokens: 52 -> 44 us), except grouped float32 ones
         // with at most a workgroup per CU and K in one or two 512-byte slabs of the register-staged
         // tile, a round trip each (layer of 64 tokens, K = 128 and 256: 44.1 us a step, 45.0 with the
         // ring). What is left (dense bf16, K no whole number of 128-byte pieces, operands past 4 GiB)

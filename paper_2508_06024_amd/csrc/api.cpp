@@ -665,6 +665,11 @@ struct FitWs {
     FitSideWs side[2];
 };
 
+// Row pitch of the fit's float32 matrices of n columns, and the K of the power step: whole 16-byte
+// pieces, which the products read and write (n = h need not be a multiple of 4). Past n the
+// transposed iterate is zero and the Gram matrix repeats its last column.
+int fit_pitch(int n) { return (n + 3) & ~3; }
+
 FitWs fit_ws(const ec2moe_codec_desc* d) {
     const size_t eb = elem_bytes(static_cast<DType>(d->dtype));
     const size_t cells = static_cast<size_t>(std::max(1, d->n_slices)) * d->h * d->w;
@@ -675,10 +680,11 @@ FitWs fit_ws(const ec2moe_codec_desc* d) {
     for (int q = 0; q < 2; ++q) {
         const size_t n = static_cast<size_t>(q == 0 ? d->h : d->w), r = static_cast<size_t>(q == 0 ? d->r_h : d->r_w);
         FitSideWs& b = w.side[q];
-        b.gram = o; o += up(n * n * 4);
+        const size_t pitch = static_cast<size_t>(fit_pitch(static_cast<int>(n)));
+        b.gram = o; o += up(n * pitch * 4);
         b.y = o; o += up(n * r * 4);
         b.q1 = o; o += up(n * r * 4);
-        b.q = o; o += up(n * r * 4);
+        b.q = o; o += up(pitch * r * 4);
         b.g64 = o; o += up(r * r * 8);
         b.g64part = o; o += up(static_cast<size_t>(gram64_chunks(static_cast<int>(n), static_cast<int>(r))) * r * r * 8);
         b.f = o; o += up(chol_factor_bytes(static_cast<int>(r)));
@@ -687,11 +693,12 @@ FitWs fit_ws(const ec2moe_codec_desc* d) {
     return w;
 }
 
+// out [rows][fit_pitch(N)]
 hipError_t dense_gemm(DType dt, OutType ot, const void* tok, const void* wt, int64_t rows, int K, int N, void* out,
                       const char* name, float* part, hipStream_t s) {
     GemmArgs g{};
     g.tok = tok; g.row_index = nullptr; g.w = wt; g.w_group_stride = 0; g.seg = nullptr; g.n_groups = 1;
-    g.rows = rows; g.K = K; g.N = N; g.out = out; g.ldo = N; g.name = name;
+    g.rows = rows; g.K = K; g.N = N; g.out = out; g.ldo = fit_pitch(N); g.name = name;
     g.src_rows = rows; g.w_rows = N; g.part = part; g.max_split = kMaxSplit;
     return launch_gemm(dt, Epilogue::Store, ot, g, s);
 }
@@ -706,8 +713,8 @@ struct FitSide {
     float* last;  // receives the last iterate [n][r]
 };
 
-// Q = orth(src) of both sides: one Cholesky QR pass into q as [r][n] (the GEMM's weight rows of the
-// next power step), or for the last iterate two passes (CholeskyQR2) into last as [n][r].
+// Q = orth(src) of both sides: one Cholesky QR pass into q as [r][fit_pitch(n)] (the GEMM's
+// weight rows of the next power step), or for the last iterate two passes (CholeskyQR2) into last as [n][r].
 hipError_t orthonormalise(const FitSide (&f)[2], bool last, int32_t* zero_status, int32_t* status, hipStream_t s) {
     for (int pass = 0; pass < (last ? 2 : 1); ++pass) {
         GramSide gs[2];
@@ -718,7 +725,7 @@ hipError_t orthonormalise(const FitSide (&f)[2], bool last, int32_t* zero_status
             const float* in = pass == 0 ? f[q].src : f[q].q1;
             gs[q] = GramSide{in, f[q].n, f[q].r, f[q].g64part, f[q].g64};
             ca.s[q] = CholSide{f[q].g64, f[q].f, f[q].r};
-            sa.s[q] = SolveSide{in, f[q].f, !last ? f[q].q : (pass == 0 ? f[q].q1 : f[q].last), f[q].n, f[q].r, !last};
+            sa.s[q] = SolveSide{in, f[q].f, !last ? f[q].q : (pass == 0 ? f[q].q1 : f[q].last), f[q].n, f[q].r, !last ? fit_pitch(f[q].n) : 0};
         }
         hipError_t e = launch_gram64(gs, pass == 0 ? zero_status : nullptr, s);
         if (e == hipSuccess) e = launch_chol(ca, s);
@@ -781,7 +788,8 @@ ec2moe_status ec2moe_lowrank_fit(const ec2moe_codec_desc* desc, const void* x, c
     // both sides in lockstep: orthonormalise the start blocks, then iters steps Q = orth(gram Q)
     for (int it = 0; it <= iters && e == hipSuccess; ++it) {
         for (int q = 0; q < 2 && it > 0 && e == hipSuccess; ++q) {
-            e = dense_gemm(DType::F32, OutType::Same, f[q].gram, f[q].q, f[q].n, f[q].n, f[q].r, f[q].y, "fit_power", part, stream);
+            e = dense_gemm(DType::F32, OutType::Same, f[q].gram, f[q].q, f[q].n, fit_pitch(f[q].n), f[q].r, f[q].y,
+                           "fit_power", part, stream);
             f[q].src = f[q].y;
         }
         if (e == hipSuccess) e = orthonormalise(f, it == iters, it == 0 ? status : nullptr, status, stream);

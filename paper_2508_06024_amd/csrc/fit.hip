@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kCholThreads) void chol_kernel(CholArgs args) {
 // Y as the 16 x 16 blocks of Y^T in float64 registers; per block row k, Q^T_k = R_kk^-T Y^T_k and
 // Y^T_j -= R_kj^T Q^T_k for j > k (as many products as a multiplication by the triangular
 // inverse, which would cost the factorisation twice its products). The factor's row k + 1 is
-// loaded while row k is applied from LDS. Out: float32 [n][r], or [r][n] when transposed.
+// loaded while row k is applied from LDS. Out: float32 [n][r], or [r][ldt] with zeros past n.
 constexpr int kSolveWaves = 4;
 
 __global__ __launch_bounds__(64 * kSolveWaves, 1) void solve_kernel(SolveArgs args) {
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(64 * kSolveWaves, 1) void solve_kernel(SolveArgs ar
     if (static_cast<int>(blockIdx.x) * 16 * kSolveWaves >= n) return;
     const Block64* f = static_cast<const Block64*>(side.f);
     const int t = (blockIdx.x * kSolveWaves + wave) * 16 + l16;
-    const bool live = t < n;
+    const bool live = t < (side.ldt ? side.ldt : n);  // n <= ldt <= n + 3, inside the last workgroup's 64 rows
     const float* __restrict__ yrow = side.y + static_cast<int64_t>(min(t, n - 1)) * r + g;
     f64x4 m[kCholMaxB];
 #pragma unroll
@@ -344,8 +344,8 @@ __global__ __launch_bounds__(64 * kSolveWaves, 1) void solve_kernel(SolveArgs ar
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int i = 16 * k + 4 * v + g;
-                    const int64_t at = side.transposed ? static_cast<int64_t>(i) * n + t : static_cast<int64_t>(t) * r + i;
-                    side.out[at] = static_cast<float>(x[v]);
+                    const int64_t at = side.ldt ? static_cast<int64_t>(i) * side.ldt + t : static_cast<int64_t>(t) * r + i;
+                    side.out[at] = t < n ? static_cast<float>(x[v]) : 0.f;
                 }
             }
         }

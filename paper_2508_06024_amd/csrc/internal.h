@@ -138,12 +138,13 @@ struct CholArgs {
 };
 size_t chol_factor_bytes(int r);
 hipError_t launch_chol(const CholArgs& a, hipStream_t s);
-// out = y R^-1 (y [n][r] float32, float64 arithmetic, rounded once): [n][r], or [r][n] when transposed
+// out = y R^-1 (y [n][r] float32, float64 arithmetic, rounded once): [n][r], or transposed to [r][ldt]
+// when ldt > 0 (at most 3 more than n: zeros past n)
 struct SolveSide {
     const float* y;
     const void* f;
     float* out;
-    int n, r, transposed;
+    int n, r, ldt;
 };
 struct SolveArgs {
     SolveSide s[2];

@@ -821,8 +821,13 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
             bf16x4 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(acc[e]);
+            // zeros past r_h, also where V_hat holds an infinity or NaN (0 times either is NaN)
+            uint2 bits = __builtin_bit_cast(uint2, o);
+            const uint32_t keep = 16 * ib < rh ? ~0u : 0u;
+            bits.x &= keep;
+            bits.y &= keep;
             const int R = 16 * wave + l16;
-            *reinterpret_cast<bf16x4*>(buf0 + R * ROWB + (((2 * ib + (g >> 1)) ^ ex_swz<RH>(R)) * 16) + (g & 1) * 8) = o;
+            *reinterpret_cast<uint2*>(buf0 + R * ROWB + (((2 * ib + (g >> 1)) ^ ex_swz<RH>(R)) * 16) + (g & 1) * 8) = bits;
         }
     };
     auto barrier = [&]() {  // with this wave's LDS accesses done

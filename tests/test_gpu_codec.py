@@ -7,7 +7,7 @@ import torch
 import oracle as O
 from paper_2508_06024_amd import ec2moe as E
 from paper_2508_06024_amd import workload as W
-from tests.gpu_common import TOL_F32, assert_close, down, say, tol, up
+from tests.gpu_common import TOL_F32, assert_close, down, say, tol, up, up_f32
 
 pytestmark = pytest.mark.gpu
 
@@ -83,6 +83,26 @@ def test_codec_slices_and_separate_decoder_projections(c, h, w, rh, rw, dt):
         rz = O.lowrank_encode(f(x[s]), f(u), f(v))
         assert_close(down(z[s]), rz, TOL_F32, f"Z[{s}]")
         assert_close(down(xh[s]), O.lowrank_decode(rz, f(uh), f(vh)), tol(dt), f"X_hat[{s}]")
+
+
+@pytest.mark.parametrize("c,h,w,rh,rw", [
+    (1, 130, 256, 16, 32),    # one launch, rank padded to 32
+    (2, 130, 256, 48, 64),    # ... to 64
+    (1, 200, 384, 112, 112),  # ... to 128
+    (1, 150, 256, 144, 64),   # two launches, rank padded to 256
+])
+def test_infinity_in_a_padded_rank_reaches_only_its_own_column(c, h, w, rh, rw):
+    """An infinite projection value of one model column: with positive factors that column of X_hat is
+    +inf in every token, and every other column is finite."""
+    rng = np.random.default_rng(rh)
+    pos = lambda *shape: W.f32_to_bf16_bits(rng.uniform(0.5, 1.0, shape).astype(np.float32))
+    uh, vh = pos(h, rh), pos(w, rw)
+    vh[w // 2, rw // 3] = 0x7F80
+    z = rng.uniform(0.5, 1.0, (c, rh, rw)).astype(np.float32)
+    got = down(E.lowrank_decode(up_f32(z), up(uh, W.BF16), up(vh, W.BF16)))
+    hit = np.arange(w) == w // 2
+    assert np.all(np.isposinf(got[..., hit]))
+    assert np.all(np.isfinite(got[..., ~hit]))
 
 
 def test_codec_is_deterministic():

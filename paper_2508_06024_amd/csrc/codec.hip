@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <string>
+#include <type_traits>
 
 namespace ec2moe {
 namespace {
@@ -662,8 +663,7 @@ __global__ __launch_bounds__(256) void dec_small_kernel(const float* __restrict_
 // holds the U_hat operand fragments of its 32 tokens in registers for the whole run; the chunks'
 // Wt rows (64 x RH, K-contiguous) stream through two LDS buffers by buffer_load ... lds. A chunk's
 // results wait in registers (packed to bf16) and are stored behind the issue of the loads of the
-// chunk after the next, and the wait for those loads leaves the stores in flight (loads and stores
-// leave vmcnt in the order of their issue). Two workgroups per CU overlap each other's waits.
+// chunk after the next. Two workgroups per CU overlap each other's waits.
 // Wt is the A operand of v_mfma_f32_16x16x32_bf16 with its rows permuted: operand row m = 4 g + e
 // of block b is column 16 g + 4 b + e of the chunk, so a lane's 16 results of one token are 16
 // consecutive columns. Each wave passes its 32 x 64 results through 4 KB of LDS so that every
@@ -689,7 +689,10 @@ __device__ __forceinline__ int ex_swz(int r) {
 // FUSED (r_w at most ex_fused_rw(RH)): no Wt comes from memory. The workgroup keeps bf16(Z[s]) in LDS and
 // forms the Wt rows of a chunk itself, wave w those of columns 16 w .. + 15 (V_hat's rows straight into
 // operand registers, loaded a chunk ahead), with the same roundings.
-template <int RH, bool FUSED>
+// EXACT: whole bands (h a multiple of 128) and r_h = RH, known at compile time, so that no load or
+// store tests its token or rank (4096 x 4096 ranks 128: 15.9 us with the tests, 15.6 without; 2048 x
+// 4096 ranks 256: 16.5 and 16.3).
+template <int RH, bool FUSED, bool EXACT>
 __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict__ u_hat, const bf16_t* __restrict__ wt,
                                                        const float* __restrict__ z, const bf16_t* __restrict__ v_hat,
                                                        int h, int w, int rh, int rw, int cpw, bf16_t* __restrict__ x_hat) {
@@ -709,7 +712,7 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
     const int nranges = (nch + cpw - 1) / cpw;
     const int band = blockIdx.x / nranges;
     const int c0 = (blockIdx.x % nranges) * cpw, c1 = min(c0 + cpw, nch);
-    const bool whole = (band + 1) * kExT <= h;
+    const bool whole = EXACT || (band + 1) * kExT <= h;
     if (!FUSED) wt += (static_cast<int64_t>(blockIdx.y) * w + static_cast<int64_t>(c0) * kExC) * RH;
     x_hat += static_cast<int64_t>(blockIdx.y) * h * w;
 
@@ -735,7 +738,7 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
         f32x4 zv[ZQ];
 #pragma unroll
         for (int q = 0; q < ZQ; ++q)
-            zv[q] = zr + ZS * q < rh && 4 * zc < rw
+            zv[q] = (EXACT || zr + ZS * q < rh) && 4 * zc < rw
                         ? *reinterpret_cast<const f32x4*>(z + (static_cast<int64_t>(blockIdx.y) * rh + zr + ZS * q) * rw + 4 * zc)
                         : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -752,10 +755,11 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
     uint4 fb[2][KS];
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-        const int t = min(band * kExT + 32 * wave + 16 * n + l16, h - 1);
-        const bf16_t* urow = u_hat + static_cast<int64_t>(t) * rh + 8 * g;
+        const int tok = band * kExT + 32 * wave + 16 * n + l16;
+        const bf16_t* urow = u_hat + static_cast<int64_t>(EXACT ? tok : min(tok, h - 1)) * (EXACT ? RH : rh) + 8 * g;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) fb[n][s] = 32 * s + 8 * g < rh ? ldg16(urow + 32 * s) : make_uint4(0, 0, 0, 0);
+        for (int s = 0; s < KS; ++s)
+            fb[n][s] = EXACT || 32 * s + 8 * g < rh ? ldg16(urow + 32 * s) : make_uint4(0, 0, 0, 0);
     }
 
     // DMA: instruction j of the wave fills bytes 1024 (NLD wave + j) .. + 1023 of a buffer, i.e.
@@ -823,7 +827,7 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
             for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(acc[e]);
             // zeros past r_h, also where V_hat holds an infinity or NaN (0 times either is NaN)
             uint2 bits = __builtin_bit_cast(uint2, o);
-            const uint32_t keep = 16 * ib < rh ? ~0u : 0u;
+            const uint32_t keep = EXACT || 16 * ib < rh ? ~0u : 0u;
             bits.x &= keep;
             bits.y &= keep;
             const int R = 16 * wave + l16;
@@ -841,17 +845,15 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
         const bool odd = !FUSED && ((c - c0) & 1);
         const char* cur = odd ? buf1 : buf0;
         char* nxt = odd ? buf0 : buf1;
-        // this chunk's rows are in LDS; after the barrier every wave is done reading the other
-        // buffer, which is refilled next. The four stores of a whole band that follow the loads stay
-        // in flight (a ragged band may skip some of its stores, so it waits for them all).
+        // this chunk's rows are in LDS (and the stores issued before its products are done); after the
+        // barrier every wave is done reading the other buffer, which is refilled next
         if constexpr (FUSED) {
             barrier();  // Z is staged; every wave is done reading the previous chunk's rows
             form_w();
             if (c + 1 < c1) load_v();
             barrier();
         } else {
-            if (whole && c > c0 + 1) __builtin_amdgcn_s_waitcnt(0x0070 | 4);
-            else __builtin_amdgcn_s_waitcnt(0x0070);
+            __builtin_amdgcn_s_waitcnt(0x0070);
             __builtin_amdgcn_sched_barrier(0);
             asm volatile("s_barrier" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
@@ -921,6 +923,8 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
 constexpr int kVztT = 64;                // rows j and rows i per workgroup
 constexpr int kVztPitch = 256 * 2 + 16;  // LDS bytes per staged row (r_w <= 256, 16 bytes of skew)
 
+// EXACT: r_h = ldw, so the rows have no padding.
+template <bool EXACT>
 __global__ __launch_bounds__(256) void vzt_kernel(const float* __restrict__ z, const bf16_t* __restrict__ v_hat,
                                                   int w, int rh, int rw, int ldw, bf16_t* __restrict__ wt) {
     __shared__ __attribute__((aligned(16))) char zs[kVztT * kVztPitch];
@@ -982,14 +986,14 @@ __global__ __launch_bounds__(256) void vzt_kernel(const float* __restrict__ z, c
                                                          acc, 0, 0, 0);
     // lane: row j of Wt, columns i0 + 32 wi + 8 q + 4 lh + e of acc[4 q + e]
     const int j = j0 + 32 * wj + l32;
-    bf16_t* out = wt + (static_cast<int64_t>(s) * w + j) * ldw;
+    bf16_t* out = wt + (static_cast<int64_t>(s) * w + j) * (EXACT ? rh : ldw);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int i = i0 + 32 * wi + 8 * q + 4 * lh;
-        if (i < ldw) {  // r_h is a multiple of 4: the run of four is whole; zeros past it
+        if (i < (EXACT ? rh : ldw)) {  // r_h is a multiple of 4: the run of four is whole; zeros past it
             bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(i < rh ? acc[4 * q + e] : 0.f);
+            for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(EXACT || i < rh ? acc[4 * q + e] : 0.f);
             *reinterpret_cast<bf16x4*>(out + i) = o;
         }
     }
@@ -1193,7 +1197,8 @@ hipError_t launch_decode_bf16(const float* z, const void* u_hat, const void* v_h
     const bool fused = rw <= ex_fused_rw(rp) && (rp <= 64 || bands * nch * slices <= 512);
     if (!fused) {
         ProfileScope prof("codec_vzt", s);
-        hipLaunchKernelGGL(vzt_kernel, dim3(w / kVztT, (rp + kVztT - 1) / kVztT, slices), dim3(256), 0, s, z,
+        hipLaunchKernelGGL((rh == rp ? &vzt_kernel<true> : &vzt_kernel<false>),
+                           dim3(w / kVztT, (rp + kVztT - 1) / kVztT, slices), dim3(256), 0, s, z,
                            static_cast<const bf16_t*>(v_hat), w, rh, rw, rp, static_cast<bf16_t*>(wt));
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1207,16 +1212,21 @@ hipError_t launch_decode_bf16(const float* z, const void* u_hat, const void* v_h
                            static_cast<const bf16_t*>(wt), z, static_cast<const bf16_t*>(v_hat), h, w, rh, rw, cpw,
                            static_cast<bf16_t*>(x_hat));
     };
-    if (fused) {
-        if (rp == 32) go(&expand_kernel<32, true>);
-        else if (rp == 64) go(&expand_kernel<64, true>);
-        else go(&expand_kernel<128, true>);
-    } else {
-        if (rp == 32) go(&expand_kernel<32, false>);
-        else if (rp == 64) go(&expand_kernel<64, false>);
-        else if (rp == 128) go(&expand_kernel<128, false>);
-        else go(&expand_kernel<256, false>);
-    }
+    auto pick = [&](auto exact) {
+        constexpr bool X = decltype(exact)::value;
+        if (fused) {
+            if (rp == 32) go(&expand_kernel<32, true, X>);
+            else if (rp == 64) go(&expand_kernel<64, true, X>);
+            else go(&expand_kernel<128, true, X>);
+        } else {
+            if (rp == 32) go(&expand_kernel<32, false, X>);
+            else if (rp == 64) go(&expand_kernel<64, false, X>);
+            else if (rp == 128) go(&expand_kernel<128, false, X>);
+            else go(&expand_kernel<256, false, X>);
+        }
+    };
+    if (h % kExT == 0 && rh == rp) pick(std::true_type{});
+    else pick(std::false_type{});
     return hipGetLastError();
 }
 

@@ -163,6 +163,7 @@ struct CodecWs {
     int tc;      // tokens per chunk of the U^T P contraction
     bool fused;  // bf16 layers: P and U^T P in one kernel
     int ks;      // its shares of the width
+    int runs;    // its runs of 64-token tiles
     bool small;  // at most 64 tokens per slice: the small-batch encoder and decoder
     // decode: W = V_hat Z^T per slice; float32 layers: the segment offsets and row maps of the
     // grouped products over a batch of slices
@@ -196,8 +197,9 @@ CodecWs codec_ws(const ec2moe_codec_desc* d) {
     w.small = codec_small_ok(d->h, d->w, d->r_h, d->r_w);
     w.fused = !w.small && d->dtype == EC2MOE_BF16;
     w.ks = w.fused ? encode_splits(d->h, d->w, d->r_w, w.batch) : 1;
-    // partial sums of U^T P: per token chunk, or per 64-token tile and share of the width
-    const size_t chunks = w.fused ? (static_cast<size_t>(d->h) + 63) / 64 * w.ks
+    w.runs = w.fused ? encode_runs(d->h, d->r_h, d->r_w, w.batch) : 1;
+    // partial sums of U^T P: per token chunk, or per run of 64-token tiles and share of the width
+    const size_t chunks = w.fused ? static_cast<size_t>(w.runs) * w.ks
                                   : (static_cast<size_t>(std::max(1, d->h)) + w.tc - 1) / w.tc;
     size_t o = 0;
     w.gpart = o; o += up(gemm_split_scratch_bytes());
@@ -549,7 +551,7 @@ ec2moe_status ec2moe_lowrank_encode(const ec2moe_codec_desc* desc, const void* x
         if (w.fused) {
             EncArgs a{};
             a.x = static_cast<const char*>(x) + c0 * slice_bytes; a.v = v; a.u = u; a.part = at<float>(ws, w.epart);
-            a.h = desc->h; a.w = desc->w; a.rh = desc->r_h; a.rw = desc->r_w; a.slices = nc; a.ks = w.ks;
+            a.h = desc->h; a.w = desc->w; a.rh = desc->r_h; a.rw = desc->r_w; a.slices = nc; a.ks = w.ks; a.runs = w.runs;
             e = launch_encode_fused(a, z + static_cast<size_t>(c0) * desc->r_h * desc->r_w, stream);
             continue;
         }

@@ -174,14 +174,15 @@ __global__ __launch_bounds__(256) void utp_kernel(UtpArgs g) {
 
 // ------------------------------------------------------------------ fused encoder (bf16 layers)
 //
-// One workgroup per (64-token tile, 64-column tile, share of the width) of P = X V: the tile's
-// products over its share, then at once that share's part of Z = U^T P,
-//   part[s][tt][kq][r][c] = sum over the tile's tokens t of U[t][r] P_kq[t][c],
-// which split_reduce_kernel adds over token tiles and shares in order (Z is linear in P, so the
-// shares of P need not be added first). X and V (as stored, [w][r_w]) stream through a ring of
-// four LDS stages of 128 model columns (32 KB: 64 token rows of 256 bytes, and the 128 rows of V
-// for those model columns, 128 bytes each: the tile's 64 columns) filled by buffer_load ... lds,
-// so three stages are in flight while one is consumed. V's operand fragments need 8 consecutive
+// One workgroup per (run of 64-token tiles, 64-column tile, share of the width) of P = X V: a tile's
+// products over the share, then at once that share's part of Z = U^T P,
+//   part[s][tr][kq][r][c] = sum over the run's tokens t of U[t][r] P_kq[t][c],
+// which split_reduce_kernel adds over runs and shares in order (Z is linear in P, so the
+// shares of P need not be added first). A run is one tile, or where many tiles would leave many
+// partial sums a longer one, its sums over the tiles staying in registers (RUNS; encode_runs()).
+// X and V (as stored, [w][r_w]) stream through a ring of four LDS stages of 128 model columns (32 KB:
+// 64 token rows of 256 bytes, and the 128 rows of V for those model columns, 128 bytes each: the
+// tile's 64 columns) filled by buffer_load ... lds, so three stages are in flight while one is consumed. V's operand fragments need 8 consecutive
 // model columns per lane, which run down the staged rows: the gfx950 transposing LDS read
 // (ds_read_b64_tr_b16) gathers them, 4 rows at a time. Eight waves, two k-steps of every stage
 // for half the tokens each; their sums meet in LDS. The P tile is then split exactly into three bf16 planes, p = hi +
@@ -247,6 +248,12 @@ __host__ __device__ inline int enc_stage(int w, int ks, int q) {
     return static_cast<int>(static_cast<int64_t>(w / kEncK) * q / ks);
 }
 
+// first token tile of run q of `runs`
+__device__ inline int enc_tile(int tiles, int runs, int q) {
+    return static_cast<int>(static_cast<int64_t>(tiles) * q / runs);
+}
+
+template <bool RUNS>
 __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
     // one LDS object per ring slot, each named at compile time where it is read, so the wait
     // before a fragment read only covers the DMA into that slot
@@ -256,9 +263,10 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
     __shared__ __attribute__((aligned(1024))) char lds3[kEncStage];
     static_assert(kEncT * kEncRow == kEncK * kEncC * 2, "token rows and V rows fill equal halves of a stage");
     const int ct_n = (a.rw + kEncC - 1) / kEncC, tt_n = (a.h + kEncT - 1) / kEncT;
-    const int n = ct_n * tt_n * a.ks * a.slices;
+    const int runs = RUNS ? a.runs : tt_n;
+    const int n = ct_n * runs * a.ks * a.slices;
     const int g = blockIdx.x;
-    int ct, xt;  // column tile; (slice, token tile, share of the width)
+    int ct, xt;  // column tile; (slice, run of token tiles, share of the width)
     if (n % (8 * ct_n) == 0) {
         // the column tiles of one block of X run on one XCD (workgroups go round-robin over the
         // eight): X rows are fetched into that XCD's L2 once for all of them
@@ -269,15 +277,25 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
         ct = g % ct_n;
         xt = g / ct_n;
     }
-    const int kq = xt % a.ks, tts = xt / a.ks;
-    const int s = tts / tt_n, tt = tts % tt_n;
-    const int valid = min(kEncT, a.h - tt * kEncT);  // tokens of this tile
+    const int kq = xt % a.ks, trs = xt / a.ks;
+    const int s = trs / runs, tr = trs % runs;
     const int st0 = enc_stage(a.w, a.ks, kq), ns = enc_stage(a.w, a.ks, kq + 1) - st0;
+    const int tt1 = RUNS ? enc_tile(tt_n, runs, tr + 1) : tr + 1;
 
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
+    // Z share: wave w owns rows 64 (w & 3) .. + 63 of U^T P and the 32 columns 32 (w >> 2) ..
+    const int rbase = 64 * (wave & 3), cb = wave >> 2;
+    f32x16 z[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[i][r] = 0.f;
+
+    for (int tt = RUNS ? enc_tile(tt_n, runs, tr) : tr; tt < tt1; ++tt) {
+    const int valid = min(kEncT, a.h - tt * kEncT);  // tokens of this tile
     const uint32_t row_bytes = static_cast<uint32_t>(a.w) * 2u;
 
     // U^T staging items (8 tokens x 8 rows of U^T each), loaded first: their loads are older
@@ -465,30 +483,27 @@ __global__ __launch_bounds__(512, 1) void encode_fused_kernel(EncArgs a) {
     }
     __syncthreads();
 
-    // Z share: wave w owns rows 64 (w & 3) .. + 63 of U^T P and the 32 columns 32 (w >> 2) ..
-    const int rbase = 64 * (wave & 3), cb = wave >> 2;
-    if (rbase >= a.rh) return;
-    f32x16 z[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) z[i][r] = 0.f;
     const int sw = (l32 >> 1) & 7;
+    if (rbase < a.rh) {
 #pragma unroll
-    for (int q = 0; q < kEncT / 16; ++q) {
-        const int ch = ((2 * q + lh) ^ sw) * 16;
-        uint4 ua[2], pb[3];
+        for (int q = 0; q < kEncT / 16; ++q) {
+            const int ch = ((2 * q + lh) ^ sw) * 16;
+            uint4 ua[2], pb[3];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) ua[i] = *reinterpret_cast<const uint4*>(lds_u + (rbase + 32 * i + l32) * 128 + ch);
+            for (int i = 0; i < 2; ++i) ua[i] = *reinterpret_cast<const uint4*>(lds_u + (rbase + 32 * i + l32) * 128 + ch);
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) pb[pl] = *reinterpret_cast<const uint4*>(lds_p + (pl * kEncC + 32 * cb + l32) * 128 + ch);
+            for (int pl = 0; pl < 3; ++pl) pb[pl] = *reinterpret_cast<const uint4*>(lds_p + (pl * kEncC + 32 * cb + l32) * 128 + ch);
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl)
+            for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                z[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ua[i]), __builtin_bit_cast(bf16x8, pb[pl]),
-                                                               z[i], 0, 0, 0);
+                for (int i = 0; i < 2; ++i)
+                    z[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ua[i]), __builtin_bit_cast(bf16x8, pb[pl]),
+                                                                   z[i], 0, 0, 0);
+        }
     }
+    if (RUNS) __syncthreads();  // every wave is done with U^T and the planes: the next tile's stages take their slots
+    }
+    if (rbase >= a.rh) return;
     float* part = a.part + static_cast<int64_t>(xt) * a.rh * a.rw;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -1112,18 +1127,33 @@ int encode_splits(int h, int w, int rw, int slices) {
     return static_cast<int>(ks);
 }
 
+int encode_runs(int h, int rh, int rw, int slices) {
+    // A run has one partial sum of r_h x r_w floats. One per tile while that is cheap: up to two rounds
+    // of tiles, or 16 MiB of partial sums (33000 x 2048 ranks 32 x 64, 516 tiles and 4 MB: 61.8 us a
+    // tile each, 69.7 in runs). Past both, one round of workgroups, with at most 16 MiB for any h
+    // (20001 x 512 ranks 256: 72.8 us a tile each, 37.4 in runs; 100001 x 512 ranks 256: 362 and 163;
+    // 8256 x 4096 ranks 256, 516 tiles: 86.3 and 66.5).
+    const int64_t ct_n = (rw + kEncC - 1) / kEncC, tt_n = (h + kEncT - 1) / kEncT;
+    if (ct_n * tt_n * slices <= 512 || tt_n * slices * rh * rw * 4 <= (int64_t(16) << 20)) return static_cast<int>(tt_n);
+    return static_cast<int>(std::max<int64_t>(1, 256 / (ct_n * slices)));
+}
+
 hipError_t launch_encode_fused(const EncArgs& a, float* z, hipStream_t s) {
-    const int tt_n = ((a.h + kEncT - 1) / kEncT) * a.ks;
+    const int parts = a.runs * a.ks;
     {
         ProfileScope prof("codec_encode", s);
-        hipLaunchKernelGGL(encode_fused_kernel, dim3(((a.rw + kEncC - 1) / kEncC) * tt_n * a.slices), dim3(512), 0, s, a);
+        const dim3 grid(((a.rw + kEncC - 1) / kEncC) * parts * a.slices);
+        if (a.runs == (a.h + kEncT - 1) / kEncT)
+            hipLaunchKernelGGL(encode_fused_kernel<false>, grid, dim3(512), 0, s, a);
+        else
+            hipLaunchKernelGGL(encode_fused_kernel<true>, grid, dim3(512), 0, s, a);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t mn = static_cast<int64_t>(a.rh) * a.rw;
     const int rgrid = static_cast<int>(std::min<int64_t>((mn + 255) / 256, 4096));
     ProfileScope prof("codec_utp_reduce", s);
-    hipLaunchKernelGGL(split_reduce_kernel<float>, dim3(rgrid, a.slices), dim3(256), 0, s, a.part, mn, tt_n, z);
+    hipLaunchKernelGGL(split_reduce_kernel<float>, dim3(rgrid, a.slices), dim3(256), 0, s, a.part, mn, parts, z);
     return hipGetLastError();
 }
 

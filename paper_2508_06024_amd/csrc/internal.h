@@ -80,9 +80,10 @@ struct UtpArgs {
     float* z;
 };
 hipError_t launch_utp(const UtpArgs& g, hipStream_t s);
-// Fused encoder of bf16 layers: part[s][tt][kq][r][c] = U^T (X V) over 64-token tiles tt and
-// ks = encode_splits() shares kq of the width (X [slices][h][w], V [w][r_w], U [h][r_h]; w a multiple
-// of 128), then z[s] = the sum over tt and kq in order. part holds slices * ceil(h / 64) * ks * r_h * r_w floats.
+// Fused encoder of bf16 layers: part[s][tr][kq][r][c] = U^T (X V) over runs = encode_runs() runs tr of
+// 64-token tiles and ks = encode_splits() shares kq of the width (X [slices][h][w], V [w][r_w],
+// U [h][r_h]; w a multiple of 128), then z[s] = the sum over tr and kq in order. part holds
+// slices * runs * ks * r_h * r_w floats. runs and ks hold for all launches with at most `slices` slices.
 struct EncArgs {
     const void* x;   // bf16
     const void* v;   // bf16
@@ -90,7 +91,9 @@ struct EncArgs {
     float* part;
     int h, w, rh, rw, slices;
     int ks;          // shares of the width: encode_splits()
+    int runs;        // runs of token tiles: encode_runs()
 };
+int encode_runs(int h, int rh, int rw, int slices);
 int encode_splits(int h, int w, int rw, int slices);
 // Small batches (h <= 64 tokens per slice, r_h <= 64): the encoder in two launches through
 // part (codec_small_part_floats floats) and the decoder in one, in float32 throughout.

@@ -215,6 +215,15 @@ def test_codec_validation():
     assert size(r_w=512, w=1024)[0] == UNSUPPORTED
 
 
+@pytest.mark.parametrize("w,rh,rw,c", [(512, 256, 256, 1), (4096, 256, 256, 4), (128, 16, 128, 16), (2048, 144, 208, 2)])
+def test_codec_workspace_does_not_grow_with_the_length(w, rh, rw, c):
+    """bf16 encoder: at most two rounds of 256 partial sums of r_h x 64 floats, or 16 MiB of them, for any
+    h; the decoder's W and the shared scratch do not depend on h."""
+    size = lambda h: E.lowrank_workspace_size(E.codec_desc(h, w, rh, rw, E.BF16, c))
+    short = size(257)
+    assert all(size(h) <= short + max(512 * rh * 64 * 4, 16 << 20) for h in (5000, 20001, 65536, 100001, 400000))
+
+
 def test_profile_collect_without_records():
     assert E.profile_collect() == {}
 

@@ -62,6 +62,10 @@ def test_full_rank_codec_round_trips_on_gpu():
     (1, 65, 1152, 64, 16, W.BF16),     # 9 stages in 4 shares, one token in the second tile
     (1, 127, 128, 16, 80, W.BF16),     # one stage
     (2, 1000, 640, 144, 208, W.BF16),  # tiles of two slices in one share
+    # ... and many token tiles with large partial sums, in runs whose sums stay in registers:
+    (1, 20001, 128, 128, 128, W.BF16),  # 313 tiles in 128 runs of two or three, 33 tokens in the last
+    (2, 8193, 256, 144, 208, W.BF16),   # 129 tiles in 32 runs of two slices, one token in the last
+    (17, 2100, 128, 128, 80, W.BF16),   # 33 tiles in 8 runs; the second batch has a single slice
     # at most 64 tokens per slice take the small-batch encoder and decoder:
     (3, 48, 256, 32, 48, W.BF16),
     (2, 64, 256, 64, 256, W.F32),     # the largest r_h and r_w of that path

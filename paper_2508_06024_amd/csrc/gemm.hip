@@ -1409,7 +1409,8 @@ template <typename T, typename TO, bool SWIGLU>
 hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
     constexpr bool kLdsPath = sizeof(T) == 2;
     const bool lds_ok = kLdsPath && a.K % 128 == 0;
-    const bool one_slab = a.seg && a.K <= 256 && grid_size<32, 128, SWIGLU>(a) <= kCUs;  // float32
+    const bool few = grid_size<32, 128, SWIGLU>(a) <= kCUs;  // at most a workgroup per CU
+    const bool one_slab = a.seg && a.K <= 256 && few;        // float32
     switch (choose_tile(a, SWIGLU, lds_ok)) {
         case Tile::Big:
             if constexpr (kLdsPath)
@@ -1419,15 +1420,17 @@ hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
             if constexpr (kLdsPath)
                 if (lds_ok) return run_lds<128, 128, 2, 2, SWIGLU, TO>(a, s);
             return run<T, TO, 128, 128, 2, 2, SWIGLU>(a, s);
-        // The streaming kernel for grouped bf16 and all float32 products (4096 x 4096 x 256 in float32:
-        // 100 -> about 80 us; 12 experts, 1024 x 512, 64 tokens: 52 -> 44 us), except grouped float32 ones
-        // with at most a workgroup per CU and K in one or two 512-byte slabs of the register-staged
-        // tile, a round trip each (layer of 64 tokens, K = 128 and 256: 44.1 us a step, 45.0 with the
-        // ring). What is left (dense bf16, K no whole number of 128-byte pieces, operands past 4 GiB)
-        // takes that tile, with wider slab rows for long K.
+        // The streaming kernel for grouped bf16 products and for the float32 ones that reach this tile
+        // (4096 x 4096 x 256 in float32: 100 -> about 80 us; 12 experts, 1024 x 512, 64 tokens: 52 -> 44 us),
+        // except grouped float32 ones with at most a workgroup per CU and K up to 256 (layer of 64
+        // tokens, K = 128 and 256: 44.1 us a step, 45.0 with the ring). What is left (dense bf16, K no
+        // whole number of 128-byte pieces, operands past 4 GiB) takes the register-staged tile, with wider
+        // slab rows for long K, and with few workgroups for K in whole 512-byte slabs, a round trip each.
+        // A K that ends inside such a slab would stage and multiply its zeros (float32 decoder, 4 x 100 x
+        // 512 ranks 32: 16.1 us, 11.3 with 128-byte rows; 300 x 2048 ranks 48: 12.4 and 9.9).
         default:
             if ((kLdsPath ? a.seg != nullptr : !one_slab) && stream_ok<T>(a)) return run_stream_for<T, TO, SWIGLU>(a, s);
-            if (a.K >= 4096 || grid_size<32, 128, SWIGLU>(a) <= kCUs) return run<T, TO, 32, 128, 1, 4, SWIGLU, 32>(a, s);
+            if (a.K >= 4096 || (few && a.K * sizeof(T) % 512 == 0)) return run<T, TO, 32, 128, 1, 4, SWIGLU, 32>(a, s);
             if (a.K >= 2048) return run<T, TO, 32, 128, 1, 4, SWIGLU, 16>(a, s);
             return run<T, TO, 32, 128, 1, 4, SWIGLU, 8>(a, s);
     }

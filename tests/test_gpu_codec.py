@@ -47,6 +47,11 @@ def test_full_rank_codec_round_trips_on_gpu():
     (4, 256, 768, 64, 64, W.BF16),   # the paper-shaped layers: 4 sequences of 256 tokens
     (1, 300, 256, 80, 64, W.BF16),   # r_h ending inside the second 64-row block of U^T P
     (2, 260, 128, 208, 112, W.F32),  # ... inside the fourth
+    # float32 products with K in no whole 512-byte slabs, dense and grouped
+    (1, 300, 512, 48, 48, W.F32),
+    (2, 200, 512, 96, 160, W.F32),
+    (4, 100, 512, 32, 32, W.F32),
+    (3, 90, 256, 80, 16, W.F32),
     # bf16 layers take the fused encoder, here in whole 64-token, 64-column tiles:
     (3, 128, 256, 80, 128, W.BF16),   # r_h inside the second 64-row block, two column tiles
     (2, 256, 384, 256, 192, W.BF16),  # three column tiles of a token tile placed on one XCD

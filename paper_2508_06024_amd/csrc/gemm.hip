@@ -66,6 +66,7 @@ struct TileInfo {
     int64_t row0;  // first row of the tile (position in the permuted order)
     int valid;     // rows of the tile inside the group
     int nt;        // n-tile index
+    int mtiles;    // token tiles of the group
 };
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -115,6 +116,7 @@ __device__ __forceinline__ bool tile_of(const GemmArgs& a, int ntn, int bid, Til
         band_decode(bid, mtiles, ntn, mt, nt);
         ti.group = 0;
         ti.nt = nt;
+        ti.mtiles = mtiles;
         ti.row0 = static_cast<int64_t>(mt) * TM;
         ti.valid = static_cast<int>(std::min<int64_t>(TM, a.rows - ti.row0));
         return true;
@@ -148,6 +150,7 @@ __device__ __forceinline__ bool tile_of(const GemmArgs& a, int ntn, int bid, Til
             int mt, nt;
             band_decode(local, mtiles, ntn, mt, nt);
             ti.nt = nt;
+            ti.mtiles = mtiles;
             ti.row0 = glo + static_cast<int64_t>(mt) * TM;
             ti.valid = std::min(TM, ghi - static_cast<int>(ti.row0));
             return true;
@@ -431,7 +434,7 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
 // two workgroups share a CU (80 KB each), so that one's start overlaps the other's stream. Four waves
 // of TM x 32 on v_mfma_f32_16x16x32_bf16; each ring slot is its own LDS object, named at compile time
 // where it is read, so that a fragment read waits for no later load.
-template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, bool NT>
+template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING>
 __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
     constexpr int CPR = 8;                  // 16-byte chunks per slab row
     constexpr int BK = CPR * Elem<T>::kPerChunk;  // elements of K per slab
@@ -478,14 +481,15 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
         }
         voff[j] = static_cast<uint32_t>(src) * row_bytes + static_cast<uint32_t>(((lane % CPR) ^ swz(R)) * 16);
     }
-    auto issue = [&](int st, char* slot) {
+    // nt: the weights pass the caches by (streaming policy)
+    auto issue = [&](auto nt, int st, char* slot) {
         char* base = slot + 1024 * NLD * wave;
 #pragma unroll
         for (int j = 0; j < NLD; ++j) {
             const bool tok = RPI * (NLD * wave + j) < TM;  // uniform
             lds_void* dst = reinterpret_cast<lds_void*>(reinterpret_cast<uintptr_t>(base + 1024 * j));
             if (tok) raw_buffer_load_lds(rtok, dst, 16, static_cast<int>(voff[j]), st * ROWB, 0, 0);
-            else raw_buffer_load_lds(rw, dst, 16, static_cast<int>(voff[j]), st * ROWB, 0, NT ? 2 : 0);
+            else raw_buffer_load_lds(rw, dst, 16, static_cast<int>(voff[j]), st * ROWB, 0, decltype(nt)::value ? 2 : 0);
         }
     };
 
@@ -509,7 +513,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
         for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int ns = a.K / BK;
-    auto step = [&](int st, const char* cur, char* refill) {
+    auto step = [&](auto nt, int st, const char* cur, char* refill) {
         if (st >= ns) return;
         // slabs issued after this one stay in flight
         const int later = std::min(RING - 2, ns - 1 - st);
@@ -521,7 +525,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        if (st + RING - 1 < ns) issue(st + RING - 1, refill);
+        if (st + RING - 1 < ns) issue(nt, st + RING - 1, refill);
 #pragma unroll
         for (int q = 0; q < CPR / 4; ++q) {
             uint4 bt[MI], aw[NI];
@@ -537,21 +541,29 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
                 for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = Mfma<T>::step(aw[ni], bt[mi], acc[ni][mi]);
         }
     };
-    issue(0, lds0);
-    if (ns > 1) issue(1, lds1);
-    if (RING == 4 && ns > 2) issue(2, lds2);
-    for (int st = 0; st < ns; st += RING) {
-        if constexpr (RING == 3) {
-            step(st, lds0, lds2);
-            step(st + 1, lds1, lds0);
-            step(st + 2, lds2, lds1);
-        } else {
-            step(st, lds0, lds3);
-            step(st + 1, lds1, lds0);
-            step(st + 2, lds2, lds1);
-            step(st + 3, lds3, lds2);
+    auto stream = [&](auto nt) {
+        issue(nt, 0, lds0);
+        if (ns > 1) issue(nt, 1, lds1);
+        if (RING == 4 && ns > 2) issue(nt, 2, lds2);
+        for (int st = 0; st < ns; st += RING) {
+            if constexpr (RING == 3) {
+                step(nt, st, lds0, lds2);
+                step(nt, st + 1, lds1, lds0);
+                step(nt, st + 2, lds2, lds1);
+            } else {
+                step(nt, st, lds0, lds3);
+                step(nt, st + 1, lds1, lds0);
+                step(nt, st + 2, lds2, lds1);
+                step(nt, st + 3, lds3, lds2);
+            }
         }
-    }
+    };
+    // The weights of a group's only token tile are read once; with more tiles they come from the caches
+    // again (40 experts of 6 rows, 4096 -> 1536 -> 4096: 237 us with the policy, 268 without; 16 active
+    // of 64 experts, 200 rows each: 333 us with it, 262 without). A loop for each: a test at every
+    // load takes 253 us in place of 237.
+    if (a.seg && uniform(ti.mtiles) == 1) stream(std::true_type{});
+    else stream(std::false_type{});
     write_tile<TO, TM, TN, 1, 4, MI, NI, SWIGLU>(a, ti, 0, wave, lane, acc);
 }
 
@@ -1282,12 +1294,12 @@ hipError_t run(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, bool NT>
+template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING>
 hipError_t run_stream(const GemmArgs& a, hipStream_t s) {
     const int64_t grid = grid_size<TM, TN, SWIGLU>(a);
     if (grid == 0) return hipSuccess;
     ProfileScope prof(a.name ? a.name : "gemm", s);
-    hipLaunchKernelGGL((gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING, NT>), dim3(static_cast<unsigned>(grid)), dim3(256),
+    hipLaunchKernelGGL((gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING>), dim3(static_cast<unsigned>(grid)), dim3(256),
                        0, s, a);
     return hipGetLastError();
 }
@@ -1378,31 +1390,23 @@ bool stream_ok(const GemmArgs& a) {
 //     239 us with 32 rows; 25 active of 64 experts, 768 -> 3072 -> 768, 1024 tokens, 90 -> 76 with 64;
 //   * 64 weight rows where 128 leave the launch under one round of two workgroups a CU: 8 experts of
 //     1-2 rows, 4096 x 8192: 247 -> 228 us with 128 rows, 219 with 64;
-//   * the weights pass the caches by (streaming policy) while a group has one token tile or so:
-//     278 -> 237 against 268 us without; 8 groups of 128 rows: 46 us with it, 42 without.
+//   * float32 products of 64 or more rows a group, and dense ones, are bound by the matrix cores: the
+//     small tile, three workgroups a CU, so that each SIMD has products to issue while another wave
+//     waits at its barrier (4 of 16 experts, 1024 -> 1024 -> 1024, 2000 tokens top-2: 289 us with 64 x
+//     128, 274 with 32 x 64).
+// The count cannot tell how the rows are spread, so the cache policy is chosen in the kernel, per group.
 template <typename T, typename TO, bool SWIGLU>
 hipError_t run_stream_for(const GemmArgs& a, hipStream_t s) {
     const int64_t rows_per_group = a.rows / std::max(1, a.n_groups);
     const int tm = rows_per_group < 16 ? 32 : 64;
     const int64_t tiles = (std::min<int64_t>(a.rows, a.n_groups) + a.rows / tm) * (a.N / 128);
     const bool narrow = !SWIGLU && tiles < 2 * kCUs;
-    // dense (float32): the small tile, three workgroups a CU, so that each SIMD has products to issue
-    // while another wave waits at its barrier
     if constexpr (!SWIGLU)
-        if (!a.seg) return run_stream<T, TO, 32, 64, SWIGLU, 4, false>(a, s);
-    if (tm == 32) {
-        if constexpr (!SWIGLU)
-            if (narrow) return run_stream<T, TO, 32, 64, SWIGLU, 4, true>(a, s);
-        return run_stream<T, TO, 32, 128, SWIGLU, 4, true>(a, s);
-    }
-    if (rows_per_group < 64) {
-        if constexpr (!SWIGLU)
-            if (narrow) return run_stream<T, TO, 64, 64, SWIGLU, 4, true>(a, s);
-        return run_stream<T, TO, 64, 128, SWIGLU, 3, true>(a, s);
-    }
+        if (!a.seg || (sizeof(T) == 4 && rows_per_group >= 64)) return run_stream<T, TO, 32, 64, SWIGLU, 4>(a, s);
     if constexpr (!SWIGLU)
-        if (narrow) return run_stream<T, TO, 64, 64, SWIGLU, 4, false>(a, s);
-    return run_stream<T, TO, 64, 128, SWIGLU, 3, false>(a, s);
+        if (narrow)
+            return tm == 32 ? run_stream<T, TO, 32, 64, SWIGLU, 4>(a, s) : run_stream<T, TO, 64, 64, SWIGLU, 4>(a, s);
+    return tm == 32 ? run_stream<T, TO, 32, 128, SWIGLU, 4>(a, s) : run_stream<T, TO, 64, 128, SWIGLU, 3>(a, s);
 }
 
 template <typename T, typename TO, bool SWIGLU>

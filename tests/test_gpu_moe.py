@@ -252,6 +252,30 @@ def test_moe_forward_streaming_tiles(T, d, M, H, k, act, dt):
     assert np.max(row_err) <= 2 * tol(dt), f"worst row {int(np.argmax(row_err))}: {np.max(row_err):.2e}"
 
 
+@pytest.mark.parametrize("T,d,M,H,act,dt", [
+    # rows a group over all groups, tile; the active groups have 0, 1, 2 and many token tiles:
+    (900, 128, 64, 1024, "relu", W.BF16),    # 14: 32 x 128, then 32 x 64
+    (1500, 256, 64, 384, "swiglu", W.BF16),  # 23: 64 x 128, slabs no multiple of the ring, then 64 x 64
+    (900, 256, 8, 384, "relu", W.F32),       # 112: 32 x 64 in both layers
+    (900, 256, 64, 256, "swiglu", W.F32),    # 14: 32 x 128 in float32
+])
+def test_moe_forward_streaming_tiles_with_few_active_experts(T, d, M, H, act, dt):
+    cfg = W.LayerConfig("masked", dt, T, d, M, 1, H, 1, 16, 16, seed=T, mask="all", x_dist="rms", activation=act)
+    inp = W.gen_layer(cfg)
+    # a group's rows: one, a tile's last row, one more, and the rest
+    sizes = [1, 32, 33, 64, 65, T - 195]
+    experts = np.linspace(0, M - 1, len(sizes)).astype(int)
+    idx = np.random.default_rng(T).permutation(np.repeat(experts, sizes)).astype(np.int32)[:, None]
+    w = np.random.default_rng(M).uniform(0.2, 1.0, (T, 1)).astype(np.float32)
+    y = E.moe_forward(up(inp.x, cfg.dtype), up_i32(idx), up_f32(w), up(inp.w_gate_up, cfg.dtype),
+                      up(inp.w_down, cfg.dtype), activation=act)
+    ry = O.moe_forward(inp.f64("x"), idx, w, W.to_f64(inp.w_gate_up, cfg.dtype), W.to_f64(inp.w_down, cfg.dtype), act)
+    got = down(y)
+    assert_close(got, ry, tol(dt), "y")
+    row_err = np.max(np.abs(got - ry), axis=1) / np.maximum(np.max(np.abs(ry), axis=1), 1e-30)
+    assert np.max(row_err) <= 2 * tol(dt), f"worst row {int(np.argmax(row_err))}: {np.max(row_err):.2e}"
+
+
 # ----------------------------------------------------------------------------- ReLU experts
 
 def _relu_cfg(name, dtype, T, d, M, K, H, k, seed, n_keep=0):

@@ -1415,6 +1415,8 @@ hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
     const bool lds_ok = kLdsPath && a.K % 128 == 0;
     const bool few = grid_size<32, 128, SWIGLU>(a) <= kCUs;  // at most a workgroup per CU
     const bool one_slab = a.seg && a.K <= 256 && few;        // float32
+    const int64_t kb = static_cast<int64_t>(a.K) * sizeof(T), zeros = (kb + 511) / 512 * 512 - kb;
+    const bool wide_ok = 8 * zeros <= kb;  // 512-byte slab rows hold little but K
     switch (choose_tile(a, SWIGLU, lds_ok)) {
         case Tile::Big:
             if constexpr (kLdsPath)
@@ -1429,12 +1431,13 @@ hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
         // except grouped float32 ones with at most a workgroup per CU and K up to 256 (layer of 64
         // tokens, K = 128 and 256: 44.1 us a step, 45.0 with the ring). What is left (dense bf16, K no
         // whole number of 128-byte pieces, operands past 4 GiB) takes the register-staged tile, with wider
-        // slab rows for long K, and with few workgroups for K in whole 512-byte slabs, a round trip each.
-        // A K that ends inside such a slab would stage and multiply its zeros (float32 decoder, 4 x 100 x
-        // 512 ranks 32: 16.1 us, 11.3 with 128-byte rows; 300 x 2048 ranks 48: 12.4 and 9.9).
+        // slab rows for long K, and with few workgroups for any K that fills 512-byte slabs, a round trip
+        // each (bf16 fit of 2 x 856 x 256, K = 512 and 1712: 173 us with 128-byte rows for 1712, 166). A short K would stage and
+        // multiply a slab's zeros (float32 decoder, 4 x 100 x 512 ranks 32: 16.1 us, 11.3 with 128-byte
+        // rows; 300 x 2048 ranks 48: 12.4 and 9.9).
         default:
             if ((kLdsPath ? a.seg != nullptr : !one_slab) && stream_ok<T>(a)) return run_stream_for<T, TO, SWIGLU>(a, s);
-            if (a.K >= 4096 || (few && a.K * sizeof(T) % 512 == 0)) return run<T, TO, 32, 128, 1, 4, SWIGLU, 32>(a, s);
+            if (a.K >= 4096 || (few && wide_ok)) return run<T, TO, 32, 128, 1, 4, SWIGLU, 32>(a, s);
             if (a.K >= 2048) return run<T, TO, 32, 128, 1, 4, SWIGLU, 16>(a, s);
             return run<T, TO, 32, 128, 1, 4, SWIGLU, 8>(a, s);
     }

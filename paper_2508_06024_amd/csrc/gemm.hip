@@ -434,7 +434,7 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
 // two workgroups share a CU (80 KB each), so that one's start overlaps the other's stream. Four waves
 // of TM x 32 on v_mfma_f32_16x16x32_bf16; each ring slot is its own LDS object, named at compile time
 // where it is read, so that a fragment read waits for no later load.
-template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING>
+template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, bool POLICY>
 __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
     constexpr int CPR = 8;                  // 16-byte chunks per slab row
     constexpr int BK = CPR * Elem<T>::kPerChunk;  // elements of K per slab
@@ -541,10 +541,10 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
                 for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = Mfma<T>::step(aw[ni], bt[mi], acc[ni][mi]);
         }
     };
+    issue(std::false_type{}, 0, lds0);
+    if (ns > 1) issue(std::false_type{}, 1, lds1);
+    if (RING == 4 && ns > 2) issue(std::false_type{}, 2, lds2);
     auto stream = [&](auto nt) {
-        issue(nt, 0, lds0);
-        if (ns > 1) issue(nt, 1, lds1);
-        if (RING == 4 && ns > 2) issue(nt, 2, lds2);
         for (int st = 0; st < ns; st += RING) {
             if constexpr (RING == 3) {
                 step(nt, st, lds0, lds2);
@@ -558,11 +558,11 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
             }
         }
     };
-    // The weights of a group's only token tile are read once; with more tiles they come from the caches
-    // again (40 experts of 6 rows, 4096 -> 1536 -> 4096: 237 us with the policy, 268 without; 16 active
-    // of 64 experts, 200 rows each: 333 us with it, 262 without). A loop for each: a test at every
-    // load takes 253 us in place of 237.
-    if (a.seg && uniform(ti.mtiles) == 1) stream(std::true_type{});
+    // POLICY: the weights of a group's only token tile are read once; with more tiles they come from
+    // the caches again (40 experts of 6 rows, 4096 -> 1536 -> 4096: 239 us with the policy, 268
+    // without; 16 active of 64 experts, 200 rows each: 333 us with it, 263 without). A loop for each: a
+    // test at every load takes 253 us in place of 239. The first slabs, before the loop, go without.
+    if (POLICY && uniform(ti.mtiles) == 1) stream(std::integral_constant<bool, POLICY>{});
     else stream(std::false_type{});
     write_tile<TO, TM, TN, 1, 4, MI, NI, SWIGLU>(a, ti, 0, wave, lane, acc);
 }
@@ -1294,12 +1294,12 @@ hipError_t run(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING>
+template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, bool POLICY>
 hipError_t run_stream(const GemmArgs& a, hipStream_t s) {
     const int64_t grid = grid_size<TM, TN, SWIGLU>(a);
     if (grid == 0) return hipSuccess;
     ProfileScope prof(a.name ? a.name : "gemm", s);
-    hipLaunchKernelGGL((gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING>), dim3(static_cast<unsigned>(grid)), dim3(256),
+    hipLaunchKernelGGL((gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING, POLICY>), dim3(static_cast<unsigned>(grid)), dim3(256),
                        0, s, a);
     return hipGetLastError();
 }
@@ -1390,23 +1390,32 @@ bool stream_ok(const GemmArgs& a) {
 //     239 us with 32 rows; 25 active of 64 experts, 768 -> 3072 -> 768, 1024 tokens, 90 -> 76 with 64;
 //   * 64 weight rows where 128 leave the launch under one round of two workgroups a CU: 8 experts of
 //     1-2 rows, 4096 x 8192: 247 -> 228 us with 128 rows, 219 with 64;
-//   * float32 products of 64 or more rows a group, and dense ones, are bound by the matrix cores: the
-//     small tile, three workgroups a CU, so that each SIMD has products to issue while another wave
-//     waits at its barrier (4 of 16 experts, 1024 -> 1024 -> 1024, 2000 tokens top-2: 289 us with 64 x
-//     128, 274 with 32 x 64).
-// The count cannot tell how the rows are spread, so the cache policy is chosen in the kernel, per group.
+//   * dense float32 products, and grouped ones of 64 or more rows a group, are bound by the matrix
+//     cores: the small tile, three workgroups a CU, so that each SIMD has products to issue while
+//     another wave waits at its barrier (4 of 16 experts, 1024 -> 1024 -> 1024, 2000 tokens top-2: 289
+//     us with 64 x 128, 275 with 32 x 64). Grouped ones only with two rounds of such tiles or more
+//     (1600 tokens top-2 of 16 experts, 512 -> 512 -> 512, 1.2 rounds: 51.7 and 56.4 us) and K past 256
+//     (float32 decoder, 3 x 1000 x 2048 ranks 128: 33.7 and 39.2 us);
+//   * below 64 rows a group the kernel chooses the cache policy of the weights for each group (the
+//     average cannot tell how the rows are spread); from there on few groups have a single tile, and
+//     the second loop's code only costs (that decoder: 36.8 us with it, 33.7 without).
 template <typename T, typename TO, bool SWIGLU>
 hipError_t run_stream_for(const GemmArgs& a, hipStream_t s) {
     const int64_t rows_per_group = a.rows / std::max(1, a.n_groups);
     const int tm = rows_per_group < 16 ? 32 : 64;
     const int64_t tiles = (std::min<int64_t>(a.rows, a.n_groups) + a.rows / tm) * (a.N / 128);
-    const bool narrow = !SWIGLU && tiles < 2 * kCUs;
-    if constexpr (!SWIGLU)
-        if (!a.seg || (sizeof(T) == 4 && rows_per_group >= 64)) return run_stream<T, TO, 32, 64, SWIGLU, 4>(a, s);
-    if constexpr (!SWIGLU)
+    const bool narrow = tiles < 2 * kCUs;
+    const bool many = rows_per_group >= 64;
+    if constexpr (!SWIGLU) {
+        const int64_t small = (std::min<int64_t>(a.rows, a.n_groups) + a.rows / 32) * (a.N / 64);
+        if (!a.seg || (sizeof(T) == 4 && many && a.K > 256 && small >= 6 * kCUs))
+            return run_stream<T, TO, 32, 64, SWIGLU, 4, false>(a, s);
+        if (narrow && tm == 32) return run_stream<T, TO, 32, 64, SWIGLU, 4, true>(a, s);
         if (narrow)
-            return tm == 32 ? run_stream<T, TO, 32, 64, SWIGLU, 4>(a, s) : run_stream<T, TO, 64, 64, SWIGLU, 4>(a, s);
-    return tm == 32 ? run_stream<T, TO, 32, 128, SWIGLU, 4>(a, s) : run_stream<T, TO, 64, 128, SWIGLU, 3>(a, s);
+            return many ? run_stream<T, TO, 64, 64, SWIGLU, 4, false>(a, s) : run_stream<T, TO, 64, 64, SWIGLU, 4, true>(a, s);
+    }
+    if (tm == 32) return run_stream<T, TO, 32, 128, SWIGLU, 4, true>(a, s);
+    return many ? run_stream<T, TO, 64, 128, SWIGLU, 3, false>(a, s) : run_stream<T, TO, 64, 128, SWIGLU, 3, true>(a, s);
 }
 
 template <typename T, typename TO, bool SWIGLU>

@@ -710,7 +710,8 @@ __device__ __forceinline__ int ex_swz(int r) {
 template <int RH, bool FUSED, bool EXACT>
 __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict__ u_hat, const bf16_t* __restrict__ wt,
                                                        const float* __restrict__ z, const bf16_t* __restrict__ v_hat,
-                                                       int h, int w, int rh, int rw, int cpw, bf16_t* __restrict__ x_hat) {
+                                                       int h, int w, int rh, int rw, int cpw, int nranges,
+                                                       bf16_t* __restrict__ x_hat) {
     constexpr int ROWB = RH * 2;         // bytes per Wt row
     constexpr int CHB = kExC * ROWB;     // bytes per chunk
     constexpr int CPR = ROWB / 16;       // 16-byte pieces per row
@@ -724,7 +725,6 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
     constexpr int ZP = RW * 2 + 16;  // pitch of the staged Z rows: 16 rows on distinct banks
     __shared__ __attribute__((aligned(16))) char zs[FUSED ? RH * ZP : 16];
     const int nch = w / kExC;
-    const int nranges = (nch + cpw - 1) / cpw;
     const int band = blockIdx.x / nranges;
     const int c0 = (blockIdx.x % nranges) * cpw, c1 = min(c0 + cpw, nch);
     const bool whole = EXACT || (band + 1) * kExT <= h;
@@ -855,8 +855,9 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
     };
-    if (!FUSED && c0 < c1) issue(c0, buf0);
-    for (int c = c0; c < c1; ++c) {
+    if (!FUSED) issue(c0, buf0);
+    int c = c0;
+    do {  // every run has a chunk
         const bool odd = !FUSED && ((c - c0) & 1);
         const char* cur = odd ? buf1 : buf0;
         char* nxt = odd ? buf0 : buf1;
@@ -921,8 +922,8 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
         // the reads are done before the next chunk's staging writes
         __builtin_amdgcn_s_waitcnt(0xC07F);
         __builtin_amdgcn_wave_barrier();
-    }
-    if (c0 < c1) store_pending(c1 - 1);
+    } while (++c < c1);
+    store_pending(c1 - 1);
 }
 
 // ------------------------------------------------------------------ decoder, W = V_hat Z^T (bf16)
@@ -1235,11 +1236,12 @@ hipError_t launch_decode_bf16(const float* z, const void* u_hat, const void* v_h
     }
     // about two workgroups per CU: the chunk runs are as short as that allows
     const int cpw = static_cast<int>(std::max<int64_t>(1, (bands * nch * slices + 511) / 512));
-    const dim3 grid(static_cast<unsigned>(bands * ((nch + cpw - 1) / cpw)), slices);
+    const int nranges = static_cast<int>((nch + cpw - 1) / cpw);
+    const dim3 grid(static_cast<unsigned>(bands * nranges), slices);
     ProfileScope prof(fused ? "codec_decode" : "codec_uw", s);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, static_cast<const bf16_t*>(u_hat),
-                           static_cast<const bf16_t*>(wt), z, static_cast<const bf16_t*>(v_hat), h, w, rh, rw, cpw,
+                           static_cast<const bf16_t*>(wt), z, static_cast<const bf16_t*>(v_hat), h, w, rh, rw, cpw, nranges,
                            static_cast<bf16_t*>(x_hat));
     };
     auto pick = [&](auto exact) {

@@ -243,9 +243,10 @@ __device__ __forceinline__ uint2 lds_read_tr16(const char* p) {
     return __builtin_bit_cast(uint2, v);
 }
 
-// first stage of share q of ks over a width of w model columns
-__host__ __device__ inline int enc_stage(int w, int ks, int q) {
-    return static_cast<int>(static_cast<int64_t>(w / kEncK) * q / ks);
+// first stage of share q of ks over a width of w model columns (at most 2^18 stages and 2^8 shares: the
+// product fits; a 64-bit division would cost every workgroup's start 0.1 us)
+__device__ inline int enc_stage(int w, int ks, int q) {
+    return static_cast<int>(static_cast<uint32_t>(w / kEncK) * static_cast<uint32_t>(q) / static_cast<uint32_t>(ks));
 }
 
 // first token tile of run q of `runs`

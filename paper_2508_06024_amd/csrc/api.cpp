@@ -349,10 +349,7 @@ ec2moe_status ec2moe_group_gate_ex(const ec2moe_moe_desc* desc, const ec2moe_gat
         REQUIRE(aligned16(opts->workspace), EC2MOE_ERR_INVALID_ARGUMENT, "gate workspace is not 16-byte aligned");
         if (need > 0) {
             a.ws = static_cast<float*>(opts->workspace);
-            // At most 16 of the splits that the workspace holds: the routing launch, one workgroup per
-            // tile, waits for a load per split (32 tokens of 4096, 72 rows: 12.6 us with 32, 12.1 with
-            // 16, 13.0 with 8). Powers of two, so fewer still divide d.
-            a.nsplit = std::min(gate_split_count(dt, desc->n_tokens, desc->d_model), 16);
+            a.nsplit = gate_split_count(dt, desc->n_tokens, desc->d_model);
         }
     }
     return hip_status(launch_gate(dt, a, stream), "gate launch");

@@ -36,7 +36,7 @@ struct GateArgs {
 };
 hipError_t launch_gate(DType dt, const GateArgs& a, hipStream_t s);
 // d-splits per 16-token tile for a small batch (1: no split) and the workspace bytes of the
-// split partials (0 when there is no split)
+// split partials (0 when there is no split; room for up to 32 splits)
 int gate_split_count(DType dt, int n_tokens, int d);
 size_t gate_split_bytes(DType dt, int n_tokens, int d, int gate_rows);
 

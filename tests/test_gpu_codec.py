@@ -63,6 +63,13 @@ def test_full_rank_codec_round_trips_on_gpu():
     (3, 129, 256, 64, 256, W.BF16),    # one launch, the largest r_w, one token in the second band
     (1, 200, 384, 112, 112, W.BF16),   # one launch with padded ranks of 128
     (1, 4096, 2176, 128, 64, W.BF16),  # runs of three chunks, the last of each band one chunk (34 chunks)
+    (2, 256, 384, 32, 48, W.BF16),     # one launch, whole bands, rank 32
+    (3, 520, 2304, 64, 256, W.BF16),   # ... five bands, the largest r_w, ragged
+    (1, 3968, 2304, 64, 256, W.BF16),  # ... whole bands, runs of three chunks
+    # two launches with a ragged last band and several chunks a workgroup:
+    (1, 4001, 2176, 128, 64, W.BF16),
+    (2, 2001, 2176, 256, 208, W.BF16),
+    (1, 4001, 2176, 144, 256, W.BF16),  # rank padded to 256
     # ... with a last tile of one token or column block, and the width in shares of unequal stages:
     (1, 65, 1152, 64, 16, W.BF16),     # 9 stages in 4 shares, one token in the second tile
     (1, 127, 128, 16, 80, W.BF16),     # one stage

@@ -86,14 +86,15 @@ def test_fit_block_edges_match_oracle_iteration(c, h, w, rh, rw, iters):
         assert np.max(np.abs(g - ref)) <= (1e-6 if iters == 0 else 1.5e-3), name
 
 
-def test_fit_ill_conditioned_iterates_stay_orthonormal():
+@pytest.mark.parametrize("iters", [1, 2, 6])
+def test_fit_ill_conditioned_iterates_stay_orthonormal(iters):
     """Singular values from 1 to 1e-3: the products with the Gram matrix have condition numbers
-    near 1e6, and one Cholesky QR pass leaves about (1e6)^2 * 2^-53 = 1e-4 of orthogonality; the
-    last iterate's second pass restores it to float32."""
+    near 1e6, and one Cholesky QR pass leaves about (1e6)^2 * 2^-53 = 1e-4 of orthogonality, which
+    the next product starts from; the last iterate's second pass restores it to float32."""
     n, r = 256, 256
     p, q = W.haar_orthonormal(3, (1,), n, n), W.haar_orthonormal(3, (2,), n, n)
     x = ((p * np.logspace(0, -3, n)) @ q.T).astype(np.float32)
-    u, v, status = E.lowrank_fit(up(x, W.F32), up_f32(_omega(n, r, 1)), up_f32(_omega(n, r, 2)), 1)
+    u, v, status = E.lowrank_fit(up(x, W.F32), up_f32(_omega(n, r, 1)), up_f32(_omega(n, r, 2)), iters)
     torch.cuda.synchronize()
     assert int(status.item()) == 0
     for g in (down(u), down(v)):

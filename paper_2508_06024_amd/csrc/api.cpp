@@ -165,7 +165,7 @@ struct CodecWs {
     int ks;      // its shares of the width
     int runs;    // its runs of 64-token tiles
     bool small;  // at most 64 tokens per slice: the small-batch encoder and decoder
-    // decode: W = V_hat Z^T per slice; float32 layers: the segment offsets and row maps of the
+    // decode: W = V_hat Z^T per slice (bf16 layers: none where one launch forms and uses it); float32 layers: the segment offsets and row maps of the
     // grouped products over a batch of slices
     size_t wt, seg_w, rows_w, seg_h, rows_h, dec_total;
 };
@@ -212,7 +212,7 @@ CodecWs codec_ws(const ec2moe_codec_desc* d) {
     w.enc_total = o;
     o = shared;
     const bool bf16 = d->dtype == EC2MOE_BF16;
-    w.wt = o; o += up(nb * d->w * (bf16 ? expand_rank(d->r_h) : d->r_h) * eb);
+    w.wt = o; o += up((bf16 ? decode_wt_elems(d->h, d->w, d->r_h, d->r_w, w.batch) : nb * d->w * d->r_h) * eb);
     w.seg_w = o; o += bf16 ? 0 : up((nb + 1) * 4);
     w.rows_w = o; o += bf16 ? 0 : up(nb * d->w * 4);
     w.seg_h = o; o += bf16 ? 0 : up((nb + 1) * 4);

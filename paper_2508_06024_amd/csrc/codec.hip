@@ -3,9 +3,9 @@
 // Z = U^T P in one workgroup per 64 x 64 tile of P); the contraction Z = U^T P of float32
 // layers on the float32 matrix cores; the in-order reduction of the
 // partial sums over token tiles or chunks; the small-batch encoder and decoder (at most 64
-// tokens per slice, float32 throughout); the decoder's first product W = V_hat bf16(Z)^T of
-// bf16 layers in one launch; and the float32 -> bfloat16 rounding of Z for the decoder's
-// other shapes. U_hat W^T, and X V outside the fused encoder, run on the matrix-core GEMM.
+// tokens per slice, float32 throughout); and the decoder of bf16 layers, X_hat = U_hat W^T with
+// W = V_hat bf16(Z)^T formed by the same kernel or by one before it. The float32 layers' X V and both
+// products of their decoder run on the matrix-core GEMM.
 #include "device_common.h"
 #include "internal.h"
 
@@ -65,13 +65,11 @@ constexpr int kUtpPP = 80;   // LDS pitch of the staged P rows (80 % 64 = 16)
 // the 64 columns c0.. of this workgroup and all r_h <= 256 rows (blockIdx.z: the slice, whose
 // P rows, partials and Z follow the previous slice's), on the float32 matrix cores
 // (v_mfma_f32_16x16x4f32: lane l feeds A[l % 16][l / 16] and B[l / 16][l % 16] and holds
-// D[4 (l / 16) + i][l % 16]). Each stage loads 64 token rows of U (converted to float32) and of
+// D[4 (l / 16) + i][l % 16]). Each stage loads 64 token rows of U and of
 // P with 16-byte loads into LDS; rows past the chunk are zero. Wave w owns rows w*64 .. w*64+63.
-template <typename TU>
 __global__ __launch_bounds__(256) void utp_kernel(UtpArgs g) {
     __shared__ float Us[kUtpT * kUtpUP];
     __shared__ float Ps[kUtpT * kUtpPP];
-    constexpr int EPC = 16 / static_cast<int>(sizeof(TU));
     const int c0 = blockIdx.x * kUtpC;
     const int tb = blockIdx.y * g.tc;
     const float* pin_ = g.p + static_cast<int64_t>(blockIdx.z) * g.T * g.rw;
@@ -94,21 +92,21 @@ __global__ __launch_bounds__(256) void utp_kernel(UtpArgs g) {
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const TU* u = static_cast<const TU*>(g.u);
+    const float* u = static_cast<const float*>(g.u);
     for (int t0 = tb; t0 < te; t0 += kUtpT) {
         const int nt = min(kUtpT, te - t0);
-        // U rows (rh / EPC chunks per row, at most 8 chunks per thread) and P rows (16 chunks
+        // U rows (rh / 4 chunks of 4 floats per row, at most 16 per thread) and P rows (16 chunks
         // of 4 floats per row, 4 per thread): all loads of the stage issue before the LDS stores
-        const int ucpr = g.rh / EPC;
-        constexpr int UPT = kUtpT * (256 / EPC) / 256;
-        uint4 uq[UPT];
+        const int ucpr = g.rh / 4;
+        constexpr int UPT = kUtpT * (256 / 4) / 256;
+        f32x4 uq[UPT];
 #pragma unroll
         for (int j = 0; j < UPT; ++j) {
             const int i = threadIdx.x + 256 * j;
             const int r = i / ucpr, ch = i % ucpr;
-            uq[j] = make_uint4(0, 0, 0, 0);
+            uq[j] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (i < kUtpT * ucpr && r < nt)
-                uq[j] = *reinterpret_cast<const uint4*>(u + static_cast<int64_t>(t0 + r) * g.rh + ch * EPC);
+                uq[j] = *reinterpret_cast<const f32x4*>(u + static_cast<int64_t>(t0 + r) * g.rh + ch * 4);
         }
         constexpr int PPT = kUtpT * 16 / 256;
         f32x4 pq[PPT];
@@ -124,12 +122,7 @@ __global__ __launch_bounds__(256) void utp_kernel(UtpArgs g) {
             const int i = threadIdx.x + 256 * j;
             if (i < kUtpT * ucpr) {
                 const int r = i / ucpr, ch = i % ucpr;
-                const TU* e = reinterpret_cast<const TU*>(&uq[j]);
-#pragma unroll
-                for (int q = 0; q < EPC; q += 4)
-                    *reinterpret_cast<f32x4*>(Us + r * kUtpUP + ch * EPC + q) =
-                        f32x4{Elem<TU>::to_f32(e[q]), Elem<TU>::to_f32(e[q + 1]), Elem<TU>::to_f32(e[q + 2]),
-                              Elem<TU>::to_f32(e[q + 3])};
+                *reinterpret_cast<f32x4*>(Us + r * kUtpUP + ch * 4) = uq[j];
             }
         }
 #pragma unroll
@@ -1029,10 +1022,9 @@ __global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float* __restric
     }
 }
 
-// Decoder set-up for n slices at once: Z rounded to bfloat16 (when zb is given), and the
-// segment offsets and row maps of the two grouped products (slice s owns rows s*w .. of
-// V_hat Z^T, gathered from row p - s*w of V_hat, and rows s*h .. of X_hat, from row p - s*h
-// of U_hat).
+// Set-up of the float32 decoder for n slices at once: the segment offsets and row maps of the two
+// grouped products (slice s owns rows s*w .. of V_hat Z^T, gathered from row p - s*w of V_hat, and
+// rows s*h .. of X_hat, from row p - s*h of U_hat).
 __global__ __launch_bounds__(256) void codec_prep_kernel(int n, int w, int h,
                                                          int32_t* __restrict__ seg_w, int32_t* __restrict__ rows_w,
                                                          int32_t* __restrict__ seg_h, int32_t* __restrict__ rows_h) {
@@ -1105,7 +1097,7 @@ hipError_t launch_utp(const UtpArgs& g, hipStream_t s) {
     dim3 grid((g.rw + kUtpC - 1) / kUtpC, chunks, g.slices);
     {
         ProfileScope prof("codec_utp", s);
-        hipLaunchKernelGGL(utp_kernel<float>, grid, dim3(256), 0, s, g);
+        hipLaunchKernelGGL(utp_kernel, grid, dim3(256), 0, s, g);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1216,17 +1208,31 @@ hipError_t launch_codec_prep(int n, int w, int h, int32_t* seg_w, int32_t* rows_
     return hipGetLastError();
 }
 
+namespace {
 int expand_rank(int rh) { return rh <= 32 ? 32 : rh <= 64 ? 64 : rh <= 128 ? 128 : 256; }
+
+// Whether the expansion kernel forms Wt itself: one launch where forming it in every band costs less
+// than the launch it saves. Padded ranks up to 64 always (4 x 256 x 768 ranks 64: 12.9 -> 7.5 us; 4096 x
+// 4096 ranks 64: 13.9 -> 13.3; at the largest r_w, 64 x 256, 19.9 us there and 61.8 for 16384 x 4096,
+// against 20.9 and 75.1 with the GEMM that these ranks took before), rank 128 up to one round of the
+// machine (4001 x 512 ranks 128 x 32: 10.0 -> 7.6 us; 1024 tiles the same; 4096 x 4096 ranks 128, 2048
+// tiles: 15.9 against 20.1 us fused).
+bool decode_one_launch(int h, int w, int rh, int rw, int slices) {
+    const int rp = expand_rank(rh);
+    const int64_t tiles = static_cast<int64_t>((h + kExT - 1) / kExT) * (w / kExC) * slices;
+    return rw <= ex_fused_rw(rp) && (rp <= 64 || tiles <= 512);
+}
+}  // namespace
+
+size_t decode_wt_elems(int h, int w, int rh, int rw, int slices) {
+    return decode_one_launch(h, w, rh, rw, slices) ? 0 : static_cast<size_t>(slices) * w * expand_rank(rh);
+}
 
 hipError_t launch_decode_bf16(const float* z, const void* u_hat, const void* v_hat, int h, int w, int rh, int rw,
                               int slices, void* wt, void* x_hat, hipStream_t s) {
     const int rp = expand_rank(rh);
-    // One launch where forming Wt in every band costs less than the launch it saves: padded ranks up
-    // to 64 always (4 x 256 x 768 ranks 64: 12.9 -> 7.5 us; 4096 x 4096 ranks 64: 13.9 -> 13.3), rank
-    // 128 up to one round of the machine (4001 x 512 ranks 128 x 32: 10.0 -> 7.6 us; 1024 tiles the
-    // same; 4096 x 4096 ranks 128, 2048 tiles: 15.9 against 20.1 us fused).
     const int64_t bands = (h + kExT - 1) / kExT, nch = w / kExC;
-    const bool fused = rw <= ex_fused_rw(rp) && (rp <= 64 || bands * nch * slices <= 512);
+    const bool fused = decode_one_launch(h, w, rh, rw, slices);
     if (!fused) {
         ProfileScope prof("codec_vzt", s);
         hipLaunchKernelGGL((rh == rp ? &vzt_kernel<true> : &vzt_kernel<false>),
@@ -1252,9 +1258,7 @@ hipError_t launch_decode_bf16(const float* z, const void* u_hat, const void* v_h
             else if (rp == 64) go(&expand_kernel<64, true, X>);
             else go(&expand_kernel<128, true, X>);
         } else {
-            if (rp == 32) go(&expand_kernel<32, false, X>);
-            else if (rp == 64) go(&expand_kernel<64, false, X>);
-            else if (rp == 128) go(&expand_kernel<128, false, X>);
+            if (rp == 128) go(&expand_kernel<128, false, X>);
             else go(&expand_kernel<256, false, X>);
         }
     };

@@ -108,10 +108,10 @@ hipError_t launch_encode_fused(const EncArgs& a, float* z, hipStream_t s);
 // rows_h[p] = p % h (s <= n).
 hipError_t launch_codec_prep(int n, int w, int h, int32_t* seg_w, int32_t* rows_w, int32_t* seg_h, int32_t* rows_h,
                              hipStream_t s);
-// Decoder of bf16 layers in two launches: Wt[s] = V_hat bf16(Z[s])^T, rounded to bf16, into wt
-// [slices][w][expand_rank(r_h)] (zeros past r_h), then X_hat[s] = U_hat Wt[s]^T (w a multiple of 128;
-// r_h, r_w multiples of 16, at most 256).
-int expand_rank(int rh);
+// Decoder of bf16 layers: Wt[s] = V_hat bf16(Z[s])^T, rounded to bf16, and X_hat[s] = U_hat Wt[s]^T (w a
+// multiple of 128; r_h, r_w multiples of 16, at most 256). wt holds decode_wt_elems() bf16 values: none
+// where one launch does both, which it also does for fewer slices.
+size_t decode_wt_elems(int h, int w, int rh, int rw, int slices);
 hipError_t launch_decode_bf16(const float* z, const void* u_hat, const void* v_hat, int h, int w, int rh, int rw,
                               int slices, void* wt, void* x_hat, hipStream_t s);
 // ---------------------------------------------------------------- codec fitting

@@ -698,10 +698,10 @@ __device__ __forceinline__ int ex_swz(int r) {
 // FUSED (r_w at most ex_fused_rw(RH)): no Wt comes from memory. The workgroup keeps bf16(Z[s]) in LDS and
 // forms the Wt rows of a chunk itself, wave w those of columns 16 w .. + 15 (V_hat's rows straight into
 // operand registers, loaded a chunk ahead), with the same roundings.
-// EXACT: whole bands (h a multiple of 128) and r_h = RH, known at compile time, so that no load or
-// store tests its token or rank (4096 x 4096 ranks 128: 15.9 us with the tests, 15.6 without; 2048 x
+// RANK: r_h = RH, and WHOLE: whole bands (h a multiple of 128), known at compile time, so that no
+// load or store tests its rank or token (4096 x 4096 ranks 128: 15.9 us with the tests, 15.6 without; 2048 x
 // 4096 ranks 256: 16.5 and 16.3).
-template <int RH, bool FUSED, bool EXACT>
+template <int RH, bool FUSED, bool RANK, bool WHOLE>
 __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict__ u_hat, const bf16_t* __restrict__ wt,
                                                        const float* __restrict__ z, const bf16_t* __restrict__ v_hat,
                                                        int h, int w, int rh, int rw, int cpw, int nranges,
@@ -721,7 +721,7 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
     const int nch = w / kExC;
     const int band = blockIdx.x / nranges;
     const int c0 = (blockIdx.x % nranges) * cpw, c1 = min(c0 + cpw, nch);
-    const bool whole = EXACT || (band + 1) * kExT <= h;
+    const bool whole = WHOLE || (band + 1) * kExT <= h;
     if (!FUSED) wt += (static_cast<int64_t>(blockIdx.y) * w + static_cast<int64_t>(c0) * kExC) * RH;
     x_hat += static_cast<int64_t>(blockIdx.y) * h * w;
 
@@ -747,7 +747,7 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
         f32x4 zv[ZQ];
 #pragma unroll
         for (int q = 0; q < ZQ; ++q)
-            zv[q] = (EXACT || zr + ZS * q < rh) && 4 * zc < rw
+            zv[q] = (RANK || zr + ZS * q < rh) && 4 * zc < rw
                         ? *reinterpret_cast<const f32x4*>(z + (static_cast<int64_t>(blockIdx.y) * rh + zr + ZS * q) * rw + 4 * zc)
                         : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -765,10 +765,10 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
         const int tok = band * kExT + 32 * wave + 16 * n + l16;
-        const bf16_t* urow = u_hat + static_cast<int64_t>(EXACT ? tok : min(tok, h - 1)) * (EXACT ? RH : rh) + 8 * g;
+        const bf16_t* urow = u_hat + static_cast<int64_t>(WHOLE ? tok : min(tok, h - 1)) * (RANK ? RH : rh) + 8 * g;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
-            fb[n][s] = EXACT || 32 * s + 8 * g < rh ? ldg16(urow + 32 * s) : make_uint4(0, 0, 0, 0);
+            fb[n][s] = RANK || 32 * s + 8 * g < rh ? ldg16(urow + 32 * s) : make_uint4(0, 0, 0, 0);
     }
 
     // DMA: instruction j of the wave fills bytes 1024 (NLD wave + j) .. + 1023 of a buffer, i.e.
@@ -819,7 +819,8 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
             if (trow + 24 < h) *reinterpret_cast<uint4*>(dst + 3 * w8) = p3;
         }
     };
-    // the chunk's Wt rows into buf0: lane holds column 16 wave + l16, rows i = 16 ib + 4 g + e
+    // the chunk's Wt rows into buf0: lane holds column 16 wave + l16, rows i = 16 ib + 4 g + e. Rows past
+    // r_h are zeros without a product: 0 times an infinity or NaN of V_hat would be NaN.
     auto form_w = [&]() {
 #pragma unroll
         for (int ib = 0; ib < RH / 16; ++ib) {
@@ -827,20 +828,15 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const bf16_t* __restrict
             const char* zrow = zs + (16 * ib + l16) * ZP + 16 * g;
 #pragma unroll
             for (int s = 0; s < VS; ++s)
-                if (32 * s < rw)
+                if (32 * s < rw && (RANK || 16 * ib < rh))
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                         __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(zrow + 64 * s)),
                         __builtin_bit_cast(bf16x8, va[FUSED ? s : 0]), acc, 0, 0, 0);
             bf16x4 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(acc[e]);
-            // zeros past r_h, also where V_hat holds an infinity or NaN (0 times either is NaN)
-            uint2 bits = __builtin_bit_cast(uint2, o);
-            const uint32_t keep = EXACT || 16 * ib < rh ? ~0u : 0u;
-            bits.x &= keep;
-            bits.y &= keep;
             const int R = 16 * wave + l16;
-            *reinterpret_cast<uint2*>(buf0 + R * ROWB + (((2 * ib + (g >> 1)) ^ ex_swz<RH>(R)) * 16) + (g & 1) * 8) = bits;
+            *reinterpret_cast<bf16x4*>(buf0 + R * ROWB + (((2 * ib + (g >> 1)) ^ ex_swz<RH>(R)) * 16) + (g & 1) * 8) = o;
         }
     };
     auto barrier = [&]() {  // with this wave's LDS accesses done
@@ -1251,19 +1247,20 @@ hipError_t launch_decode_bf16(const float* z, const void* u_hat, const void* v_h
                            static_cast<const bf16_t*>(wt), z, static_cast<const bf16_t*>(v_hat), h, w, rh, rw, cpw, nranges,
                            static_cast<bf16_t*>(x_hat));
     };
-    auto pick = [&](auto exact) {
-        constexpr bool X = decltype(exact)::value;
+    auto pick = [&](auto rank, auto whole) {
+        constexpr bool R = decltype(rank)::value, W = decltype(whole)::value;
         if (fused) {
-            if (rp == 32) go(&expand_kernel<32, true, X>);
-            else if (rp == 64) go(&expand_kernel<64, true, X>);
-            else go(&expand_kernel<128, true, X>);
+            if (rp == 32) go(&expand_kernel<32, true, R, W>);
+            else if (rp == 64) go(&expand_kernel<64, true, R, W>);
+            else go(&expand_kernel<128, true, R, W>);
         } else {
-            if (rp == 128) go(&expand_kernel<128, false, X>);
-            else go(&expand_kernel<256, false, X>);
+            if (rp == 128) go(&expand_kernel<128, false, R, W>);
+            else go(&expand_kernel<256, false, R, W>);
         }
     };
-    if (h % kExT == 0 && rh == rp) pick(std::true_type{});
-    else pick(std::false_type{});
+    if (rh != rp) pick(std::false_type{}, std::false_type{});
+    else if (h % kExT != 0) pick(std::true_type{}, std::false_type{});
+    else pick(std::true_type{}, std::true_type{});
     return hipGetLastError();
 }
 

@@ -277,7 +277,8 @@ ec2moe_status ec2moe_lowrank_fit_workspace_size(const ec2moe_codec_desc* desc, s
  * slice, the truncated SVD of X, the Eckart-Young minimiser of ||X - U U^T X V V^T||).
  * Computed by subspace iteration on the Gram matrices A = sum X_s X_s^T and B = sum
  * X_s^T X_s, starting from the given blocks and orthonormalising every iterate (the
- * positive-diagonal QR, by CholeskyQR2 with a float64 Gram matrix and factor).
+ * positive-diagonal QR, by Cholesky QR with a float64 Gram matrix, factor and triangular
+ * solve: one pass, and for the last iterate a second one, CholeskyQR2).
  *   x [c][h][w] calibration slices (layer dtype; c*h a multiple of 8);
  *   omega_u [h][r_h], omega_v [w][r_w] float32 start blocks of full column rank (random,
  *   drawn by the caller); iters >= 0 (at most 64) steps: the columns converge to the
@@ -285,8 +286,8 @@ ec2moe_status ec2moe_lowrank_fit_workspace_size(const ec2moe_codec_desc* desc, s
  *   u [h][r_h], v [w][r_w] out, layer dtype, orthonormal columns (to the layer precision);
  *   status device int32 out or NULL: 0, or 1 if a Cholesky pivot was not positive (a start
  *   block or data of rank below r: the outputs are then not orthonormal);
- *   ws of ec2moe_lowrank_fit_workspace_size bytes (two float32 Gram matrices of the larger
- *   of h and w, among others).
+ *   ws of ec2moe_lowrank_fit_workspace_size bytes (among others the float32 Gram matrices
+ *   of both sides, h^2 + w^2 values, and a copy of x).
  */
 ec2moe_status ec2moe_lowrank_fit(const ec2moe_codec_desc* desc, const void* x, const float* omega_u,
                                  const float* omega_v, int32_t iters, void* u, void* v, int32_t* status,

@@ -186,12 +186,12 @@ __global__ __launch_bounds__(256) void utp_kernel(UtpArgs g) {
 // i ^ ((R >> 1) & 7).
 //
 // What bounds it: with a tile per CU (4096 x 4096, ranks 256: 256 tiles) the 268 MB that the CUs
-// pull from L2, 23 us of the 26.5 us call; halving the LDS reads of the main loop (a wave used to
-// take one 32 x 32 block of every other k-step) left it at 26.5 us. With few tiles it is the
+// pull from L2, 22.9 us of the 25.4 us call; halving the LDS reads of the main loop (a wave used to
+// take one 32 x 32 block of every other k-step) made no difference. With few tiles it is the
 // serial walk over the width, hence the shares. Ragged tiles (rows and columns past the end repeat
 // the last one and are dropped) took a transpose, a split-K GEMM, its reduction, U^T P and another
-// reduction before: 1000 x 2048 ranks 128, 26.1 -> 13.4 us; 100 x 4096 ranks 64 x 256, 26.4 -> 11.6;
-// 2047 x 4096 ranks 256, 32.6 -> 23.0.
+// reduction before: 1000 x 2048 ranks 128, 23.9 -> 12.6 us; 100 x 4096 ranks 64 x 256, 26.4 -> 11.6;
+// 2047 x 4096 ranks 256, 32.6 -> 22.8.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -1105,10 +1105,12 @@ hipError_t launch_utp(const UtpArgs& g, hipStream_t s) {
 }
 
 int encode_splits(int h, int w, int rw, int slices) {
-    // Shares of the width while the tiles number at most half the CUs, of at least two stages
-    // each. 128 workgroups, not 256: the partial sums that a further halving adds cost what it
-    // saves (1000 x 2048 ranks 128: 13.4 us with 4 shares, 16.4 with 8, 26 with 16; 2047 x 4096
-    // ranks 256: 23.0 us with 1 share, 22.4 with 2; ranks 16: 13.4 us with 4, 14.8 with 8).
+    // Shares of the width while the tiles number at most 64, of at least two stages each, for at
+    // most 128 workgroups: the partial sums that a further halving adds cost what it saves (one
+    // sweep: 1000 x 2048 ranks 128, 13.4 us with 4 shares, 16.4 with 8, 26 with 16; 2047 x 4096 ranks
+    // 256, 23.0 us with 1 share, 22.4 with 2; ranks 16, 13.4 us with 4, 14.8 with 8). From 65 tiles on
+    // a second share saves time only where the width is long: 1040 x 4096 ranks 256, 20.9 us with 1
+    // and 18.5 with 2; 1500 x 1024 ranks 256, 13.9 and 14.5; 1100 x 2048 ranks 256 x 192, 14.5 and 15.4.
     const int64_t tiles = std::max<int64_t>(1, static_cast<int64_t>((rw + kEncC - 1) / kEncC) * ((h + kEncT - 1) / kEncT) * slices);
     const int ns = w / kEncK;
     int64_t ks = std::max<int64_t>(1, std::min<int64_t>(128 / tiles, ns / 2));

@@ -47,6 +47,7 @@ def _proj(a):
     (4, 18, 256, 16, 16, W.F32, 2, 1e-5),
     (8, 531, 128, 48, 32, W.F32, 2, 1e-5),
     (8, 131, 256, 64, 32, W.BF16, 3, 2e-2),
+    (8, 4097, 128, 32, 32, W.BF16, 1, 2e-2),  # ... through the largest matrix-core tile
 ])
 def test_fit_matches_oracle_iteration(c, h, w, rh, rw, dt, iters, tol):
     say(f"fit c={c} h={h} w={w} r={rh}x{rw} {dt} iters={iters}")

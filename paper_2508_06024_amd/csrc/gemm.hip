@@ -558,11 +558,11 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
             }
         }
     };
-    // POLICY: the weights of a group's only token tile are read once; with more tiles they come from
+    // POLICY, bf16: the weights of a group's only token tile are read once; with more tiles they come from
     // the caches again (40 experts of 6 rows, 4096 -> 1536 -> 4096: 239 us with the policy, 268
     // without; 16 active of 64 experts, 200 rows each: 333 us with it, 263 without). A loop for each: a
     // test at every load takes 253 us in place of 239. The first slabs, before the loop, go without.
-    if (POLICY && uniform(ti.mtiles) == 1) stream(std::integral_constant<bool, POLICY>{});
+    if (POLICY && (sizeof(T) == 4 || uniform(ti.mtiles) == 1)) stream(std::integral_constant<bool, POLICY>{});
     else stream(std::false_type{});
     write_tile<TO, TM, TN, 1, 4, MI, NI, SWIGLU>(a, ti, 0, wave, lane, acc);
 }
@@ -1390,31 +1390,41 @@ bool stream_ok(const GemmArgs& a) {
 //     239 us with 32 rows; 25 active of 64 experts, 768 -> 3072 -> 768, 1024 tokens, 90 -> 76 with 64;
 //   * 64 weight rows where 128 leave the launch under one round of two workgroups a CU: 8 experts of
 //     1-2 rows, 4096 x 8192: 247 -> 228 us with 128 rows, 219 with 64;
-//   * dense float32 products, and grouped ones of 64 or more rows a group, are bound by the matrix
-//     cores: the small tile, three workgroups a CU, so that each SIMD has products to issue while
-//     another wave waits at its barrier (4 of 16 experts, 1024 -> 1024 -> 1024, 2000 tokens top-2: 289
-//     us with 64 x 128, 275 with 32 x 64). Grouped ones only with two rounds of such tiles or more
-//     (1600 tokens top-2 of 16 experts, 512 -> 512 -> 512, 1.2 rounds: 51.7 and 56.4 us) and K past 256
-//     (float32 decoder, 3 x 1000 x 2048 ranks 128: 33.7 and 39.2 us);
-//   * below 64 rows a group the kernel chooses the cache policy of the weights for each group (the
-//     average cannot tell how the rows are spread); from there on few groups have a single tile, and
-//     the second loop's code only costs (that decoder: 36.8 us with it, 33.7 without).
+//   * float32 products are bound by the matrix cores, so padding counts more than a second read of the
+//     weights: 32 token rows below 64 rows a group, and above while 64 leave the launch under one round
+//     (28 of 32 experts, 1920 -> 896 -> 1920, 580 tokens top-3: 286 us with 64 rows, 228 with 32, 242
+//     with the register-staged tile; 8 experts, 512 -> 384 -> 512, 900 tokens top-1: 42.1, 31.6, 38.4);
+//   * dense float32 products, and grouped ones of 64 or more rows a group, take the small tile, three
+//     workgroups a CU, so that each SIMD has products to issue while another wave waits at its barrier
+//     (4 of 16 experts, 1024 -> 1024 -> 1024, 2000 tokens top-2: 289 us with 64 x 128, 274 with 32 x
+//     64). Grouped ones only with two rounds of such tiles or more (1600 tokens top-2 of 16 experts,
+//     512 -> 512 -> 512, 1.2 rounds: 51.7 and 56.4 us) and K past 256 (float32 decoder, 3 x 1000 x 2048
+//     ranks 128: 33.1 and 39.2 us);
+//   * below 64 rows a group the weights of bf16 products take the cache policy that fits their group,
+//     chosen in the kernel (the average cannot tell how the rows are spread), and those of float32
+//     products the streaming policy (100 of 128 experts, 640 -> 768 -> 640, 1500 tokens top-2: 119.5 us,
+//     123 with the choice); from there on few groups have a single tile, and the second loop's code
+//     only costs (that decoder: 36.8 us with it).
 template <typename T, typename TO, bool SWIGLU>
 hipError_t run_stream_for(const GemmArgs& a, hipStream_t s) {
+    constexpr bool kF32 = sizeof(T) == 4;
     const int64_t rows_per_group = a.rows / std::max(1, a.n_groups);
-    const int tm = rows_per_group < 16 ? 32 : 64;
-    const int64_t tiles = (std::min<int64_t>(a.rows, a.n_groups) + a.rows / tm) * (a.N / 128);
-    const bool narrow = tiles < 2 * kCUs;
     const bool many = rows_per_group >= 64;
+    auto tiles = [&](int tm, int tn) {
+        return (std::min<int64_t>(a.rows, a.n_groups) + a.rows / tm) * (a.N / (SWIGLU ? tn / 2 : tn));
+    };
+    const bool short_tile = kF32 ? !many || tiles(64, 128) < 2 * kCUs : rows_per_group < 16;
     if constexpr (!SWIGLU) {
-        const int64_t small = (std::min<int64_t>(a.rows, a.n_groups) + a.rows / 32) * (a.N / 64);
-        if (!a.seg || (sizeof(T) == 4 && many && a.K > 256 && small >= 6 * kCUs))
+        if (!a.seg || (kF32 && many && a.K > 256 && tiles(32, 64) >= 6 * kCUs))
             return run_stream<T, TO, 32, 64, SWIGLU, 4, false>(a, s);
-        if (narrow && tm == 32) return run_stream<T, TO, 32, 64, SWIGLU, 4, true>(a, s);
-        if (narrow)
+        if (tiles(short_tile ? 32 : 64, 128) < 2 * kCUs) {
+            if (short_tile)
+                return many ? run_stream<T, TO, 32, 64, SWIGLU, 4, false>(a, s) : run_stream<T, TO, 32, 64, SWIGLU, 4, true>(a, s);
             return many ? run_stream<T, TO, 64, 64, SWIGLU, 4, false>(a, s) : run_stream<T, TO, 64, 64, SWIGLU, 4, true>(a, s);
+        }
     }
-    if (tm == 32) return run_stream<T, TO, 32, 128, SWIGLU, 4, true>(a, s);
+    if (short_tile)
+        return many ? run_stream<T, TO, 32, 128, SWIGLU, 4, false>(a, s) : run_stream<T, TO, 32, 128, SWIGLU, 4, true>(a, s);
     return many ? run_stream<T, TO, 64, 128, SWIGLU, 3, false>(a, s) : run_stream<T, TO, 64, 128, SWIGLU, 3, true>(a, s);
 }
 

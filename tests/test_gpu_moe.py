@@ -236,7 +236,11 @@ def test_moe_forward_empty():
     (1400, 256, 16, 384, 1, "swiglu", W.BF16), # 87: 64 x 128 and 64 x 64 without the streaming policy
     (4480, 128, 64, 1024, 1, "relu", W.BF16),  # 70: 64 x 128 without it
     (9, 512, 8, 384, 1, "swiglu", W.F32),  # 1: 32 x 128 and 32 x 64 in float32
-    (600, 384, 16, 640, 1, "relu", W.F32), # 37: 64 x 64 in float32
+    (600, 384, 16, 640, 1, "relu", W.F32), # 37: 32 x 64 in float32
+    (1000, 384, 8, 640, 1, "swiglu", W.F32),  # 125: 32 x 128, under a round of 64 x 128
+    (1200, 128, 16, 640, 2, "swiglu", W.F32), # 150: 64 x 128
+    (1200, 256, 16, 1152, 2, "relu", W.F32),  # 150: 32 x 128 without SwiGLU, K = 256
+    (1200, 384, 16, 1536, 2, "relu", W.F32),  # 150: 32 x 64 over two rounds
 ])
 def test_moe_forward_streaming_tiles(T, d, M, H, k, act, dt):
     cfg = W.LayerConfig("stream", dt, T, d, M, 1, H, k, min(T, 16), 16, seed=T, mask="all", x_dist="rms", activation=act)
@@ -256,7 +260,7 @@ def test_moe_forward_streaming_tiles(T, d, M, H, k, act, dt):
     # rows a group over all groups, tile; the active groups have 0, 1, 2 and many token tiles:
     (900, 128, 64, 1024, "relu", W.BF16),    # 14: 32 x 128, then 32 x 64
     (1500, 256, 64, 384, "swiglu", W.BF16),  # 23: 64 x 128, slabs no multiple of the ring, then 64 x 64
-    (900, 256, 8, 384, "relu", W.F32),       # 112: 32 x 64 in both layers
+    (900, 256, 8, 384, "relu", W.F32),       # 112: 32 x 64 in both layers, without the policy
     (900, 256, 64, 256, "swiglu", W.F32),    # 14: 32 x 128 in float32
 ])
 def test_moe_forward_streaming_tiles_with_few_active_experts(T, d, M, H, act, dt):

@@ -434,7 +434,19 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
 // two workgroups share a CU (80 KB each), so that one's start overlaps the other's stream. Four waves
 // of TM x 32 on v_mfma_f32_16x16x32_bf16; each ring slot is its own LDS object, named at compile time
 // where it is read, so that a fragment read waits for no later load.
-template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, bool POLICY>
+//
+// Cache policy of the weights: a group's only token tile reads them once and lets them pass the caches
+// by (streaming policy); with more tiles they come from the caches again (40 experts of 6 rows, 4096 ->
+// 1536 -> 4096: 239 us with the policy, 268 without; 16 active of 64 experts, 200 rows each: 333 us with
+// it, 263 without). Bf16 products choose by the group in the kernel (Group), with a loop for each: a
+// test at every load takes 253 us in place of 239. For K of 2048 and more the first slabs, before the
+// loops, go without (GroupLong; at K = 4096, the 40 experts: 238 -> 234 us). For short K that costs what
+// they cache (10 experts of 12 rows, 512 -> 5632 -> 512: 55.0 -> 61.1). Float32 products take the policy whatever the group, but for the first slabs,
+// which the group's further tiles find in the caches (Stream; 100 of 128 experts, 640 -> 768 -> 640, 1500
+// tokens top-2: 119.5 us, 123 with the choice, 123.5 with the first slabs streamed too).
+enum class Policy { None, Group, GroupLong, Stream };
+
+template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, Policy P>
 __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
     constexpr int CPR = 8;                  // 16-byte chunks per slab row
     constexpr int BK = CPR * Elem<T>::kPerChunk;  // elements of K per slab
@@ -541,10 +553,14 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
                 for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = Mfma<T>::step(aw[ni], bt[mi], acc[ni][mi]);
         }
     };
-    issue(std::false_type{}, 0, lds0);
-    if (ns > 1) issue(std::false_type{}, 1, lds1);
-    if (RING == 4 && ns > 2) issue(std::false_type{}, 2, lds2);
+    auto first = [&](auto nt) {
+        issue(nt, 0, lds0);
+        if (ns > 1) issue(nt, 1, lds1);
+        if (RING == 4 && ns > 2) issue(nt, 2, lds2);
+    };
+    if constexpr (P != Policy::Group) first(std::false_type{});
     auto stream = [&](auto nt) {
+        if constexpr (P == Policy::Group) first(nt);
         for (int st = 0; st < ns; st += RING) {
             if constexpr (RING == 3) {
                 step(nt, st, lds0, lds2);
@@ -558,12 +574,12 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs a) {
             }
         }
     };
-    // POLICY, bf16: the weights of a group's only token tile are read once; with more tiles they come from
-    // the caches again (40 experts of 6 rows, 4096 -> 1536 -> 4096: 239 us with the policy, 268
-    // without; 16 active of 64 experts, 200 rows each: 333 us with it, 263 without). A loop for each: a
-    // test at every load takes 253 us in place of 239. The first slabs, before the loop, go without.
-    if (POLICY && (sizeof(T) == 4 || uniform(ti.mtiles) == 1)) stream(std::integral_constant<bool, POLICY>{});
-    else stream(std::false_type{});
+    if constexpr (P == Policy::None) {
+        stream(std::false_type{});
+    } else {
+        if (P == Policy::Stream || uniform(ti.mtiles) == 1) stream(std::true_type{});
+        else stream(std::false_type{});
+    }
     write_tile<TO, TM, TN, 1, 4, MI, NI, SWIGLU>(a, ti, 0, wave, lane, acc);
 }
 
@@ -1294,14 +1310,19 @@ hipError_t run(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, bool POLICY>
-hipError_t run_stream(const GemmArgs& a, hipStream_t s) {
+template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING>
+hipError_t run_stream(const GemmArgs& a, bool policy, hipStream_t s) {
     const int64_t grid = grid_size<TM, TN, SWIGLU>(a);
     if (grid == 0) return hipSuccess;
     ProfileScope prof(a.name ? a.name : "gemm", s);
-    hipLaunchKernelGGL((gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING, POLICY>), dim3(static_cast<unsigned>(grid)), dim3(256),
-                       0, s, a);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
+        return hipGetLastError();
+    };
+    if (!policy) return go(&gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING, Policy::None>);
+    if constexpr (sizeof(T) == 4) return go(&gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING, Policy::Stream>);
+    else if (a.K < 2048) return go(&gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING, Policy::Group>);
+    else return go(&gemm_stream_kernel<T, TO, TM, TN, SWIGLU, RING, Policy::GroupLong>);
 }
 
 template <int TM, int TN, int WM, int WN, bool SWIGLU, typename TO>
@@ -1391,7 +1412,8 @@ bool stream_ok(const GemmArgs& a) {
 //   * 64 weight rows where 128 leave the launch under one round of two workgroups a CU: 8 experts of
 //     1-2 rows, 4096 x 8192: 247 -> 228 us with 128 rows, 219 with 64;
 //   * float32 products are bound by the matrix cores, so padding counts more than a second read of the
-//     weights: 32 token rows below 64 rows a group, and above while 64 leave the launch under one round
+//     weights: 32 token rows below 64 rows a group, and above, for K past 256 (shorter K, the float32
+//     decoder's, has too little to amortise a tile's start), while 64 leave the launch under one round
 //     (28 of 32 experts, 1920 -> 896 -> 1920, 580 tokens top-3: 286 us with 64 rows, 228 with 32, 242
 //     with the register-staged tile; 8 experts, 512 -> 384 -> 512, 900 tokens top-1: 42.1, 31.6, 38.4);
 //   * dense float32 products, and grouped ones of 64 or more rows a group, take the small tile, three
@@ -1400,11 +1422,8 @@ bool stream_ok(const GemmArgs& a) {
 //     64). Grouped ones only with two rounds of such tiles or more (1600 tokens top-2 of 16 experts,
 //     512 -> 512 -> 512, 1.2 rounds: 51.7 and 56.4 us) and K past 256 (float32 decoder, 3 x 1000 x 2048
 //     ranks 128: 33.1 and 39.2 us);
-//   * below 64 rows a group the weights of bf16 products take the cache policy that fits their group,
-//     chosen in the kernel (the average cannot tell how the rows are spread), and those of float32
-//     products the streaming policy (100 of 128 experts, 640 -> 768 -> 640, 1500 tokens top-2: 119.5 us,
-//     123 with the choice); from there on few groups have a single tile, and the second loop's code
-//     only costs (that decoder: 36.8 us with it).
+//   * a cache policy for the weights below 64 rows a group; from there on few groups have a single
+//     tile, and a second loop's code only costs (that decoder: 36.8 us with it).
 template <typename T, typename TO, bool SWIGLU>
 hipError_t run_stream_for(const GemmArgs& a, hipStream_t s) {
     constexpr bool kF32 = sizeof(T) == 4;
@@ -1413,19 +1432,14 @@ hipError_t run_stream_for(const GemmArgs& a, hipStream_t s) {
     auto tiles = [&](int tm, int tn) {
         return (std::min<int64_t>(a.rows, a.n_groups) + a.rows / tm) * (a.N / (SWIGLU ? tn / 2 : tn));
     };
-    const bool short_tile = kF32 ? !many || tiles(64, 128) < 2 * kCUs : rows_per_group < 16;
+    const bool short_tile = kF32 ? !many || (a.K > 256 && tiles(64, 128) < 2 * kCUs) : rows_per_group < 16;
     if constexpr (!SWIGLU) {
         if (!a.seg || (kF32 && many && a.K > 256 && tiles(32, 64) >= 6 * kCUs))
-            return run_stream<T, TO, 32, 64, SWIGLU, 4, false>(a, s);
-        if (tiles(short_tile ? 32 : 64, 128) < 2 * kCUs) {
-            if (short_tile)
-                return many ? run_stream<T, TO, 32, 64, SWIGLU, 4, false>(a, s) : run_stream<T, TO, 32, 64, SWIGLU, 4, true>(a, s);
-            return many ? run_stream<T, TO, 64, 64, SWIGLU, 4, false>(a, s) : run_stream<T, TO, 64, 64, SWIGLU, 4, true>(a, s);
-        }
+            return run_stream<T, TO, 32, 64, SWIGLU, 4>(a, false, s);
+        if (tiles(short_tile ? 32 : 64, 128) < 2 * kCUs)
+            return short_tile ? run_stream<T, TO, 32, 64, SWIGLU, 4>(a, !many, s) : run_stream<T, TO, 64, 64, SWIGLU, 4>(a, !many, s);
     }
-    if (short_tile)
-        return many ? run_stream<T, TO, 32, 128, SWIGLU, 4, false>(a, s) : run_stream<T, TO, 32, 128, SWIGLU, 4, true>(a, s);
-    return many ? run_stream<T, TO, 64, 128, SWIGLU, 3, false>(a, s) : run_stream<T, TO, 64, 128, SWIGLU, 3, true>(a, s);
+    return short_tile ? run_stream<T, TO, 32, 128, SWIGLU, 4>(a, !many, s) : run_stream<T, TO, 64, 128, SWIGLU, 3>(a, !many, s);
 }
 
 template <typename T, typename TO, bool SWIGLU>

@@ -441,9 +441,10 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
 // it, 263 without). Bf16 products choose by the group in the kernel (Group), with a loop for each: a
 // test at every load takes 253 us in place of 239. For K of 2048 and more the first slabs, before the
 // loops, go without (GroupLong; at K = 4096, the 40 experts: 238 -> 234 us). For short K that costs what
-// they cache (10 experts of 12 rows, 512 -> 5632 -> 512: 55.0 -> 61.1). Float32 products take the policy whatever the group, but for the first slabs,
-// which the group's further tiles find in the caches (Stream; 100 of 128 experts, 640 -> 768 -> 640, 1500
-// tokens top-2: 119.5 us, 123 with the choice, 123.5 with the first slabs streamed too).
+// they cache (10 experts of 12 rows, 512 -> 5632 -> 512: 55.0 -> 61.1). Float32 products take the policy
+// whatever the group, but for the first slabs, which the group's further tiles find in the caches
+// (Stream; 100 of 128 experts, 640 -> 768 -> 640, 1500 tokens top-2: 119.5 us, 123 with the choice, 123.5
+// with the first slabs streamed too).
 enum class Policy { None, Group, GroupLong, Stream };
 
 template <typename T, typename TO, int TM, int TN, bool SWIGLU, int RING, Policy P>

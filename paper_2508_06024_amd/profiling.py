@@ -32,10 +32,12 @@ _SHORT = [
     (r"gemm_kernel<ec2moe::bf16_t, float, (\d+), (\d+), \d, \d, false(?:, (\d+))?>", "gemm store bf16->f32 {0}x{1}"),
     (r"gemm_kernel<float, float, (\d+), (\d+), \d, \d, (?:true|false)(?:, (\d+))?>", "gemm f32 {0}x{1}"),
 ]
+_POLICY = ("None", "Group", "GroupLong", "Stream")  # of the streaming GEMM's weights
 
 
 def short_name(n: str) -> str:
     n = n.replace("(anonymous namespace)::", "")
+    n = re.sub(r"\((?:ec2moe::)?Policy\)(\d)", lambda m: _POLICY[int(m.group(1))], n)
     for pat, rep in _SHORT:
         m = re.search(pat, n)
         if m:
